@@ -12,7 +12,7 @@
 // tree), so the fit is deterministic.
 #pragma once
 
-#include "device_common.hpp"
+#include "verify_kernels.hpp"
 
 namespace ts {
 
@@ -20,16 +20,24 @@ constexpr int kCalibThreads = 256;
 constexpr int kFitThreads = 1024;
 
 // One workgroup per request.  parent, token, log_q0: [R][cap] (host tree
-// copied up); greedy[off[q] + i]: the target argmax of row i of request q,
-// for i <= n[q].  Outputs [R][cap]: x = logit q0, y in {0, 1}, sel in {0, 1};
+// copied up); part[(off[q] + i) * nchunks + c]: the argmax of piece c of the
+// target row i of request q, for i <= n[q], reduced here to greedy[off[q] + i].  Outputs [R][cap]: x = logit q0, y in {0, 1}, sel in {0, 1};
 // row 0 and rows past n: x NaN, y -1, sel 0.
 __global__ __launch_bounds__(kCalibThreads) void calib_labels_kernel(
     const int32_t* parent, const int32_t* token, const float* log_q0, const int32_t* n, int cap,
-    const int32_t* greedy, const int32_t* off, float* x, int32_t* y, int32_t* sel) {
+    const ArgmaxPart* part, int nchunks, int32_t* greedy, const int32_t* off, float* x, int32_t* y, int32_t* sel) {
   const int q = blockIdx.x;
   const int nq = min(max(n[q], 0), cap - 1);
   const size_t b = (size_t)q * cap;
-  const int32_t* gq = greedy + off[q];
+  int32_t* gq = greedy + off[q];
+  for (int i = threadIdx.x; i <= nq; i += kCalibThreads) {
+    const ArgmaxPart* pi = part + (size_t)(off[q] + i) * nchunks;
+    ArgmaxPart best = pi[0];
+    for (int c = 1; c < nchunks; ++c)
+      if (argmax_better(pi[c], best)) best = pi[c];
+    gq[i] = best.id;
+  }
+  __syncthreads();
   for (int i = threadIdx.x; i < cap; i += kCalibThreads) {
     float xi = __builtin_nanf("");
     int32_t yi = -1, si = 0;

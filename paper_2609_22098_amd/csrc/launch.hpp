@@ -23,8 +23,11 @@ template <typename TE, int KS>
 void launch_merge_t(const MergeParams& p, int mode, dim3 grid, dim3 block, hipStream_t s);
 
 // Verification.
-void launch_verify_argmax(const void* target, bool bf16, int V, const int* rows, int nrows,
-                          int* argmax_out, float* gap_out, hipStream_t s);
+// Pieces a row is cut into for the argmax of nrows rows (at most `most`), and
+// the launch: part [nrows][nchunks].
+int verify_argmax_chunks(int V, int nrows, bool bf16, int most);
+void launch_verify_argmax(const void* target, bool bf16, int V, const int* rows, int nrows, int nchunks,
+                          ArgmaxPart* part, hipStream_t s);
 // Tree attention mask and position ids, one workgroup per request.
 void launch_tree_mask(const int32_t* parent, const int32_t* n, int R, int cap, const int32_t* pos_offset,
                       uint32_t* mask, int32_t* pos, hipStream_t s);
@@ -35,8 +38,8 @@ void launch_wave_control(const WaveParams& wp, int w, hipStream_t s);
 void launch_wave_tree(const WaveParams& wp, const WaveTreeOut& o, const WaveTreeOut& o2, hipStream_t s);
 // Calibration: greedy labels of host-built trees, and the two-scalar fit.
 void launch_calib_labels(const int32_t* parent, const int32_t* token, const float* log_q0, const int32_t* n,
-                         int R, int cap, const int32_t* greedy, const int32_t* off, float* x, int32_t* y,
-                         int32_t* sel, hipStream_t s);
+                         int R, int cap, const ArgmaxPart* part, int nchunks, int32_t* greedy, const int32_t* off,
+                         float* x, int32_t* y, int32_t* sel, hipStream_t s);
 void launch_calib_fit(const float* x, const int32_t* y, const int32_t* sel, int n, int max_iter, double tol,
                       float* out, hipStream_t s);
 // One level of the T > 0 walk: pass A, stages 1..max(mmax, 1), bonus, resolve.

@@ -689,7 +689,7 @@ const KidIndex& kid_index(const ts_tree* t) {
 }
 
 struct VerifyLayout {
-  size_t off_rows, off_arg, off_gap, off_items, off_z, off_exp;
+  size_t off_items, off_z, off_exp;
   size_t off_pa, off_zp, off_bp, off_cst, off_rec, off_sync, bytes;
   int max_chunks;
 };
@@ -745,10 +745,7 @@ VerifyLayout verify_layout(const ts_drafter* d, int cap, float T) {
   VerifyLayout v{};
   size_t o = 0;
   if (T == 0.0f) {
-    const size_t rows = (size_t)d->R * cap;
-    v.off_rows = o; o += align256(rows * 4);
-    v.off_arg = o; o += align256(rows * 4);
-    v.off_gap = o; o += align256(rows * 4);
+    o = 256;  // the greedy walk works in the pinned staging buffer; 0 would mean an error
   } else {
     v.off_items = o; o += align256((size_t)d->R * sizeof(VerifyItem));
     v.off_z = o; o += align256((size_t)d->R * d->V * 4);
@@ -1142,39 +1139,71 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   for (int q = 0; q < R; ++q) path_len[q] = 0;
 
   if (T == 0.0f) {
-    // children of every node in creation order
-    const KidIndex& kids = kid_index(tree);
-    std::vector<int> rows;
-    for (int q = 0; q < R; ++q)
-      for (int i = 0; i <= tree->n[q]; ++i) rows.push_back(q * cap + i);
-    const int nrows = (int)rows.size();
-    int* drows = reinterpret_cast<int*>(ws + vl.off_rows);
-    int* darg = reinterpret_cast<int*>(ws + vl.off_arg);
-    float* dgap = reinterpret_cast<float*>(ws + vl.off_gap);
-    char* hs = nullptr;
-    if ((rc = host_stage((size_t)nrows * 8, &hs)) != TS_OK) return rc;
-    std::memcpy(hs, rows.data(), (size_t)nrows * 4);
-    TS_HIP(hipMemcpyAsync(drows, hs, nrows * 4, hipMemcpyHostToDevice, s));
-    launch_verify_argmax(target, target_dtype == TS_BF16, V, drows, nrows, darg, dgap, s);
-    TS_HIP(hipGetLastError());
-    const int* arg = reinterpret_cast<const int*>(hs + (size_t)nrows * 4);
-    TS_HIP(hipMemcpyAsync(hs + (size_t)nrows * 4, darg, nrows * 4, hipMemcpyDeviceToHost, s));
-    TS_HIP(hipStreamSynchronize(s));
-    int base = 0;
-    for (int q = 0; q < R; ++q) {
-      int cur = 0, len = 0;
-      for (;;) {
-        const int gtok = arg[base + cur];
-        int next = -1;
-        const int* ch = kids.first(q, cur);
-        for (int j = 0, m = kids.count(q, cur); j < m; ++j)
-          if (tree->token[(size_t)q * cap + ch[j]] == gtok) { next = ch[j]; break; }
-        if (next < 0 || len >= TS_MAX_D) { bonus[q] = gtok; break; }
-        path_nodes[(size_t)q * TS_MAX_D + len++] = next;
-        cur = next;
+    // Rounds of one argmax launch each: the rows where the walks stand, and
+    // as many levels of their descendants as fit kGreedyBytes (the walks then
+    // go on without another launch).  A launch and its synchronisation cost
+    // about 15 us, in which the GPU reads some 70 MB of rows: reading a few
+    // rows that no walk visits is cheaper than a round more, reading every
+    // row of a large batch is not (64 trees of 64 nodes, V = 151936: 1.3 GB).
+    constexpr size_t kGreedyBytes = 96u << 20, kGreedyRows = 1u << 20;
+    const KidIndex& kids = kid_index(tree);  // children of every node in creation order
+    const bool bf16 = target_dtype == TS_BF16;
+    const size_t row_bytes = (size_t)V * (bf16 ? 2 : 4);
+    std::vector<int> cur(R, 0), active(R), rows, known((size_t)R * cap, -1);
+    for (int q = 0; q < R; ++q) active[q] = q;
+    while (!active.empty()) {
+      rows.clear();
+      for (int q : active) rows.push_back(q * cap + cur[q]);
+      for (size_t level = 0;;) {
+        const size_t end = rows.size();
+        size_t more = 0;
+        for (size_t i = level; i < end; ++i) more += kids.count(rows[i] / cap, rows[i] % cap);
+        if (more == 0 || (end + more) * row_bytes > kGreedyBytes || end + more > kGreedyRows) break;
+        for (size_t i = level; i < end; ++i) {
+          const int q = rows[i] / cap, p = rows[i] % cap;
+          const int* ch = kids.first(q, p);
+          for (int j = 0, m = kids.count(q, p); j < m; ++j) rows.push_back(q * cap + ch[j]);
+        }
+        level = end;
       }
-      path_len[q] = len;
-      base += tree->n[q] + 1;
+      const int nrows = (int)rows.size();
+      const int nc = verify_argmax_chunks(V, nrows, bf16, 64);
+      const size_t hs_rows = align256((size_t)nrows * 4);
+      char* hs = nullptr;
+      if ((rc = host_stage(hs_rows + (size_t)nrows * nc * sizeof(ArgmaxPart), &hs)) != TS_OK) return rc;
+      std::memcpy(hs, rows.data(), (size_t)nrows * 4);
+      // the kernel reads the row list from the pinned buffer and writes its parts there
+      const ArgmaxPart* part = reinterpret_cast<const ArgmaxPart*>(hs + hs_rows);
+      launch_verify_argmax(target, bf16, V, reinterpret_cast<const int*>(hs), nrows, nc,
+                           reinterpret_cast<ArgmaxPart*>(hs + hs_rows), s);
+      TS_HIP(hipGetLastError());
+      for (int i = 0; i < nrows; ++i) known[rows[i]] = i;
+      TS_HIP(hipStreamSynchronize(s));
+      size_t left = 0;
+      for (int q : active) {
+        bool done = false;
+        for (int i; !done && (i = known[(size_t)q * cap + cur[q]]) >= 0;) {
+          const ArgmaxPart* pi = part + (size_t)i * nc;
+          ArgmaxPart best = pi[0];
+          for (int c = 1; c < nc; ++c)
+            if (argmax_better(pi[c], best)) best = pi[c];
+          const int gtok = best.id;
+          int next = -1;
+          const int* ch = kids.first(q, cur[q]);
+          for (int j = 0, m = kids.count(q, cur[q]); j < m; ++j)
+            if (tree->token[(size_t)q * cap + ch[j]] == gtok) { next = ch[j]; break; }
+          if (next < 0 || path_len[q] >= TS_MAX_D) {
+            bonus[q] = gtok;
+            done = true;
+          } else {
+            path_nodes[(size_t)q * TS_MAX_D + path_len[q]++] = next;
+            cur[q] = next;
+          }
+        }
+        if (!done) active[left++] = q;
+      }
+      active.resize(left);
+      for (int i = 0; i < nrows; ++i) known[rows[i]] = -1;  // the parts go with the next round's
     }
     drain.armed = false;
     return TS_OK;
@@ -1396,8 +1425,11 @@ int32_t ts_ladder_default(ts_ladder_rung* rungs, int32_t cap) {
 // ---------------------------------------------------------------- calibration
 
 namespace {
+// pieces a target row is cut into for its argmax: the parts go through the
+// workspace, whose size does not know V
+constexpr int kCalibChunks = 8;
 struct CalibLayout {
-  size_t parent, token, log_q0, n, rows, off, upload, greedy, gap, bytes;
+  size_t parent, token, log_q0, n, rows, off, upload, greedy, part, bytes;
 };
 CalibLayout calib_layout(int R, int cap) {
   CalibLayout c{};
@@ -1411,7 +1443,7 @@ CalibLayout calib_layout(int R, int cap) {
   c.off = o; o += align256((size_t)R * 4);
   c.upload = o;  // everything above is one host-to-device copy
   c.greedy = o; o += align256(rc * 4);
-  c.gap = o; o += align256(rc * 4);
+  c.part = o; o += align256(rc * kCalibChunks * sizeof(ArgmaxPart));
   c.bytes = o;
   return c;
 }
@@ -1463,12 +1495,14 @@ int32_t ts_calib_labels(const ts_tree* tree, const void* target, int32_t target_
   DrainOnError drain{s};
   TS_HIP(hipMemcpyAsync(ws, hs, cl.upload, hipMemcpyHostToDevice, s));
   int32_t* greedy = reinterpret_cast<int32_t*>(ws + cl.greedy);
-  launch_verify_argmax(target, target_dtype == TS_BF16, V, reinterpret_cast<const int*>(ws + cl.rows), nrows,
-                       greedy, reinterpret_cast<float*>(ws + cl.gap), s);
+  const int nc = verify_argmax_chunks(V, nrows, target_dtype == TS_BF16, kCalibChunks);
+  ArgmaxPart* part = reinterpret_cast<ArgmaxPart*>(ws + cl.part);
+  launch_verify_argmax(target, target_dtype == TS_BF16, V, reinterpret_cast<const int*>(ws + cl.rows), nrows, nc, part,
+                       s);
   TS_HIP(hipGetLastError());
   launch_calib_labels(reinterpret_cast<const int32_t*>(ws + cl.parent), reinterpret_cast<const int32_t*>(ws + cl.token),
                       reinterpret_cast<const float*>(ws + cl.log_q0), reinterpret_cast<const int32_t*>(ws + cl.n), R,
-                      cap, greedy, reinterpret_cast<const int32_t*>(ws + cl.off), x, y, sel, s);
+                      cap, part, nc, greedy, reinterpret_cast<const int32_t*>(ws + cl.off), x, y, sel, s);
   TS_HIP(hipGetLastError());
   TS_HIP(hipStreamSynchronize(s));
   drain.armed = false;

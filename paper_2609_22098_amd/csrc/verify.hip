@@ -1,17 +1,32 @@
 // Instantiations of the verification kernels.
+#include <algorithm>
+
 #include "launch.hpp"
 #include "verify_fused.hpp"
 
 namespace ts {
 
-void launch_verify_argmax(const void* target, bool bf16, int V, const int* rows, int nrows,
-                          int* argmax_out, float* gap_out, hipStream_t s) {
+int verify_argmax_chunks(int V, int nrows, bool bf16, int most) {
+  // a sweep of a workgroup: one 16-byte group per thread.  Pieces of four
+  // sweeps (all of a thread's loads in flight at once) unless that leaves
+  // the launch under two workgroups per CU; then down to one sweep.
+  const int sweep = kVerifyThreads * (bf16 ? 8 : 4);
+  const int sweeps = (V + sweep - 1) / sweep;
+  int c = (sweeps + 3) / 4;
+  while (c < sweeps && (long long)c * nrows < 512) ++c;
+  c = std::min(c, std::max(1, (1 << 22) / std::max(nrows, 1)));  // a launch's grid stays within its limits
+  return std::max(1, std::min(c, most));
+}
+
+void launch_verify_argmax(const void* target, bool bf16, int V, const int* rows, int nrows, int nchunks,
+                          ArgmaxPart* part, hipStream_t s) {
+  const dim3 grid((unsigned)nrows * nchunks), block(kVerifyThreads);
   if (bf16)
-    hipLaunchKernelGGL((verify_argmax_kernel<uint16_t>), dim3(nrows), dim3(kVerifyThreads), 0, s,
-                       static_cast<const uint16_t*>(target), V, rows, nrows, argmax_out, gap_out);
+    hipLaunchKernelGGL((verify_argmax_kernel<uint16_t>), grid, block, 0, s, static_cast<const uint16_t*>(target), V,
+                       rows, nchunks, part);
   else
-    hipLaunchKernelGGL((verify_argmax_kernel<float>), dim3(nrows), dim3(kVerifyThreads), 0, s,
-                       static_cast<const float*>(target), V, rows, nrows, argmax_out, gap_out);
+    hipLaunchKernelGGL((verify_argmax_kernel<float>), grid, block, 0, s, static_cast<const float*>(target), V, rows,
+                       nchunks, part);
 }
 
 template <typename TT>

@@ -1,8 +1,8 @@
 // Kernels of tree verification (ts_verify).
 //
-// T = 0 (§3.2 item 3): the greedy walk only needs the target argmax of each
-// tree row, so one kernel computes every row's argmax (ties: smallest id) and
-// the host descends the tree.
+// T = 0 (§3.2 item 3): the greedy walk only needs the target argmax of the
+// rows it visits; one kernel computes the argmax (ties: smallest id) of a
+// list of rows and the host descends the tree.
 //
 // T > 0 (§3.3, Proposition 1): at a visited node with children x_1..x_m in
 // draw order, stage j tests u_j < p_j(x_j) / q_j(x_j) where
@@ -163,65 +163,83 @@ __device__ __forceinline__ void block_argmax(float& v, int& id, float* redv, int
     if (redv[w] > v || (redv[w] == v && redi[w] < id)) { v = redv[w]; id = redi[w]; }
 }
 
-// Greedy: argmax of each existing tree row.  rows[i] = request * cap + node.
+// Greedy: the target argmax of tree rows, each row cut into nchunks pieces
+// of one workgroup each; piece c of row i leaves its best value and that
+// value's smallest token at part[i * nchunks + c], and whoever reads the
+// parts takes the best of them in (value desc, id asc) order (argmax_better).
+// rows[i] = request * cap + node; rows and part may be pinned host memory.
+//
+// The pass is bound by memory, so what counts is bytes in flight: one
+// workgroup per row left 65 of the 256 CUs with work (a tree of 64 nodes),
+// 35 us for 66 MB (260 rows, V = 128256, bf16); pieces of 8192 tokens take
+// 12 us.  Rows may start at any element: the tokens before the row's first
+// 16-byte boundary and after its last are read one by one (pieces 0 and
+// nchunks - 1), everything between in 16-byte groups of G tokens, four
+// groups of a thread in flight.  A thread sees its tokens in increasing
+// order and takes a token only if it is larger, so ties keep the smallest id
+// (a row without a finite or +inf value, or of NaNs, gives INT_MAX).
+struct ArgmaxPart {
+  float v;
+  int32_t id;
+};
+__host__ __device__ __forceinline__ bool argmax_better(const ArgmaxPart& a, const ArgmaxPart& b) {
+  return a.v > b.v || (a.v == b.v && a.id < b.id);
+}
+
 template <typename TT>
-__global__ __launch_bounds__(kVerifyThreads) void verify_argmax_kernel(const TT* target, int V,
-                                                                       const int* rows, int nrows,
-                                                                       int* argmax_out,
-                                                                       float* gap_out) {
+__global__ __launch_bounds__(kVerifyThreads) void verify_argmax_kernel(const TT* target, int V, const int* rows,
+                                                                       int nchunks, ArgmaxPart* part) {
   __shared__ float redv[4];
   __shared__ int redi[4];
-  const int i = blockIdx.x;
-  if (i >= nrows) return;
+  const int i = blockIdx.x / nchunks, c = blockIdx.x % nchunks;
   const TT* row = target + (size_t)rows[i] * V;
-  float bv = kNegInf, sv = kNegInf;
+  float bv = kNegInf;
   int bi = 0x7FFFFFFF;
   auto take = [&](float t, int y) {
-    if (t > bv) { sv = bv; bv = t; bi = y; }
-    else if (t > sv) sv = t;
+    if (t > bv) { bv = t; bi = y; }
   };
-  // 16-byte groups of G tokens (rows 16-byte aligned: V a multiple of G),
-  // four groups in flight per thread; each thread scans its tokens in
-  // increasing order, so ties keep the smallest id
   constexpr int G = 16 / (int)sizeof(TT);
-  constexpr int kStep = kVerifyThreads * G;
-  int y0 = 0;
-  if (V % G == 0 && (reinterpret_cast<uintptr_t>(target) & 15) == 0) {
-    const int nfull = V / kStep;
-    int sw = 0;
-    for (; sw < nfull; sw += 4) {
-      u32x4 w[4];
+  // tokens before the row's first 16-byte boundary
+  const int head = min(V, (int)((-(reinterpret_cast<uintptr_t>(row) / sizeof(TT))) & (G - 1)));
+  const int ngroups = (V - head) / G;
+  // this piece's groups [g0, g1)
+  const int per = (ngroups + nchunks - 1) / nchunks;
+  const int g0 = min(c * per, ngroups), g1 = min(g0 + per, ngroups);
+  if (c == 0 && (int)threadIdx.x < head) take(target_at(row, threadIdx.x), threadIdx.x);
+  const TT* body = row + head;
+  for (int gb = g0; gb < g1; gb += 4 * kVerifyThreads) {
+    u32x4 w[4];
+    const int gt = gb + (int)threadIdx.x;
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (sw + u < nfull) w[u] = *reinterpret_cast<const u32x4*>(row + (sw + u) * kStep + G * threadIdx.x);
+    for (int u = 0; u < 4; ++u)
+      w[u] = *reinterpret_cast<const u32x4*>(body + (size_t)min(gt + u * kVerifyThreads, g1 - 1) * G);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (sw + u >= nfull) break;
-        const int yb = (sw + u) * kStep + G * threadIdx.x;
+    for (int u = 0; u < 4; ++u) {
+      const int gi = gt + u * kVerifyThreads;
+      if (gi >= g1) break;
+      float t[G];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if constexpr (sizeof(TT) == 2) {
-            take(__uint_as_float(w[u][k] << 16), yb + 2 * k);
-            take(__uint_as_float(w[u][k] & 0xFFFF0000u), yb + 2 * k + 1);
-          } else {
-            take(__uint_as_float(w[u][k]), yb + k);
-          }
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (sizeof(TT) == 2) {
+          t[2 * k] = __uint_as_float(w[u][k] << 16);
+          t[2 * k + 1] = __uint_as_float(w[u][k] & 0xFFFF0000u);
+        } else {
+          t[k] = __uint_as_float(w[u][k]);
         }
       }
+      float m = t[0];
+#pragma unroll
+      for (int k = 1; k < G; ++k) m = fmaxf(m, t[k]);
+      if (m > bv) {  // rare once a few groups have been seen
+#pragma unroll
+        for (int k = 0; k < G; ++k) take(t[k], head + gi * G + k);
+      }
     }
-    y0 = nfull * kStep;
   }
-  for (int y = y0 + threadIdx.x; y < V; y += kVerifyThreads) take(target_at(row, y), y);
-  float v = bv;
-  int id = bi;
-  block_argmax(v, id, redv, redi);
-  // second-best value for near-tie reporting: the best value other than the argmax
-  float s2 = (bi == id) ? sv : bv;
-  s2 = block_max(s2, redv);
-  if (threadIdx.x == 0) {
-    argmax_out[i] = id;
-    gap_out[i] = (v - s2) / fmaxf(1.0f, fabsf(v));
-  }
+  const int tail = head + ngroups * G + (int)threadIdx.x;
+  if (c == nchunks - 1 && tail < V) take(target_at(row, tail), tail);
+  block_argmax(bv, bi, redv, redi);
+  if (threadIdx.x == 0) part[blockIdx.x] = ArgmaxPart{bv, bi};
 }
 
 struct VerifyItem {
