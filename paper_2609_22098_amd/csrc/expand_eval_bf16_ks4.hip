@@ -6,6 +6,6 @@
 #include "expand_inst.hpp"
 
 namespace ts {
-template void launch_eval_t<uint16_t, 4>(const ExpandParams&, int, int, bool, bool, dim3, dim3, hipStream_t);
-template int eval_blocks_per_cu_t<uint16_t, 4>(int, int, bool, bool, int);
+template void launch_eval_t<uint16_t, 4>(const ExpandParams&, int, int, bool, EvalPath, dim3, dim3, hipStream_t);
+template int eval_blocks_per_cu_t<uint16_t, 4>(int, int, bool, EvalPath, int);
 }  // namespace ts

@@ -596,22 +596,15 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 // two buffers used alternately, so no registers hold prefetched data.  The W2
 // tile is laid out in 16-byte pieces in the exact order the A fragments are
 // read (piece (bb*KS + kk)*64 + lane), so every fragment read is one
-// conflict-free ds_read_b128.  Requires V % 8 == 0 and chunks of a multiple of
-// 256 tokens.
+// conflict-free ds_read_b128.  Requires chunks of a multiple of 256 tokens.
 //
-// Per (parent, token) the pass spends an FMA, an exp2 and an add on each sum
-// it keeps; everything else is amortised over a lane's 16-token run or over
-// four steps:
-//   - the log-sum-exp sums are taken against a reference per parent that is
-//     raised only when a run maximum passes it by more than the headroom (one
-//     wave-wide vote per run; the raise itself is rare), instead of rescaling
-//     at every run;
-//   - with sequential draws, the q_T sum of each run is taken against the
-//     run's own maximum instead (the draws need every block's mass, however
-//     small next to the parent's largest), the block masses are combined over
-//     four steps at a time with one exchange across the lane groups and
-//     stored a 64-byte line per 16 blocks; the merge takes log-sum-exp of
-//     z / T from the block masses, so no separate sum of z / T is kept.
+// RAG: vocabularies that are no multiple of 8 tokens, whose rows of U start
+// at any 2-byte address.  A lane loads its run from the 4-byte boundary at or
+// before it, one 4-byte piece more than the aligned form, and shifts the
+// words by 0 or 16 bits once they are in registers (8 instructions per 16
+// tokens).  Before, such vocabularies took expand_eval_kernel with 16
+// two-byte loads per run: ts_expand over 512 parents, V = 100003, r = 64,
+// T = 0.7 (115 MB) went from 107 to 74 us.
 __device__ __forceinline__ void lds_dma16(const void* src, u32x4* dst_wave_base) {
   typedef __attribute__((address_space(3))) void* lds_ptr;
   __builtin_amdgcn_global_load_lds(src, (lds_ptr)dst_wave_base, 16, 0, 0);
@@ -631,6 +624,13 @@ __device__ __forceinline__ void lds_buf16_asm(u32x4 rsrc, uint32_t voff, int sof
   typedef __attribute__((address_space(3))) const void* lds_ptr;
   const uint32_t m0 = (uint32_t)(uintptr_t)(lds_ptr)dst_wave_base;
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(voff), "s"(rsrc), "s"(soff), "s"(m0) : "memory", "m0");
+}
+// The same with 4 bytes per lane, into LDS at dst_wave_base + 4 * lane.
+__device__ __forceinline__ void lds_buf4_asm(u32x4 rsrc, uint32_t voff, int soff, const uint32_t* dst_wave_base) {
+  typedef __attribute__((address_space(3))) const void* lds_ptr;
+  const uint32_t m0 = (uint32_t)(uintptr_t)(lds_ptr)dst_wave_base;
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds"
                :: "v"(voff), "s"(rsrc), "s"(soff), "s"(m0) : "memory", "m0");
 }
 // Raw buffer resource of n bytes at base, as four scalar words.
@@ -696,7 +696,7 @@ __device__ __forceinline__ void window_transpose(float (&h)[4]) {
 // waves per SIMD (168 VGPRs), four with eight-wave workgroups (128 VGPRs): a
 // few registers more halve the waves that hide its latencies.  WPG waves per
 // workgroup share each W2 tile (loaded by the first four).
-template <int KS, int NB, int MODE, int WPG>
+template <int KS, int NB, int MODE, int WPG, bool RAG>
 __global__ __launch_bounds__(64 * WPG) __attribute__((amdgpu_waves_per_eu(KS <= 2 && NB == 2 ? (WPG == 8 ? 4 : 3) : 1)))
 void expand_eval_lds_kernel(const ExpandParams p) {
   typedef Frag<uint16_t> F;
@@ -711,6 +711,9 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   __shared__ __attribute__((aligned(16))) u32x4 w1[kW];
   __shared__ __attribute__((aligned(16))) u32x4 ub0[WPG * kU];
   __shared__ __attribute__((aligned(16))) u32x4 ub1[WPG * kU];
+  constexpr int kX = RAG ? NB * 64 : 1;  // the runs' extra 4-byte pieces of one wave's U tile
+  __shared__ uint32_t ux0[RAG ? WPG * kX : 1];
+  __shared__ uint32_t ux1[RAG ? WPG * kX : 1];
   const int lane = threadIdx.x & 63;
   constexpr int BASE = MODE & 3;
   constexpr bool SAMPLE = BASE != kModeGreedy;  // T > 0: lse of z/T and K draws
@@ -742,6 +745,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   // 0: its parent's row plus its lane group's 16 tokens (U is under 4 GiB).
   // A step's loads add them to a scalar base.
   uint32_t uoff[NB];
+  uint32_t ush[NB];  // RAG: bits the run's words are shifted by, 0 or 16
   FT bfrag[NB][KS];
   uint32_t pc1[NB], pc2[NB], pc3[NB];
   int pidx[NB];
@@ -758,6 +762,8 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       }
     }
     uoff[nb] = ((uint32_t)(req * p.D + dep) * (uint32_t)V + (uint32_t)g * 16u) * 2u;
+    ush[nb] = (uoff[nb] & 2u) << 3;
+    if constexpr (RAG) uoff[nb] &= ~3u;
     const uint16_t* erow = E + (size_t)tok * r;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) bfrag[nb][kk] = F::load(erow, kk * F::kPerStep, g);
@@ -819,7 +825,9 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     woff[j] = (uint32_t)((((n >> 2) * 16 + bb * 4 + (n & 3)) * r + kk * 32 + g * 8) * 2);
   }
   const u32x4 wsrc = raw_rsrc(W2, (uint32_t)V * r * 2);
-  const u32x4 usrc = raw_rsrc(U, (uint32_t)p.R * p.D * V * 2);
+  // RAG: whole 4-byte words only (with an odd number of elements the array's
+  // last one lies past them: the last step reads it on its own)
+  const u32x4 usrc = raw_rsrc(U, (uint32_t)p.R * p.D * V * 2 & (RAG ? ~3u : ~0u));
   auto issue_w = [&](u32x4* wb, int t0) {
     if (wv < 4) {
 #pragma unroll
@@ -827,18 +835,61 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     }
   };
   typedef u32x4 UPieces[NB][2];
-  auto issue_u = [&](u32x4* ub, int t0) {
+  constexpr int kULoads = RAG ? 3 : 2;  // loads per parent block and step
+  auto issue_u = [&](u32x4* ub, uint32_t* ux, int t0) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) lds_buf16_asm(usrc, uoff[nb], t0 * 2 + 16 * h, ub + wv * kU + (nb * 2 + h) * 64);
+      if constexpr (RAG) lds_buf4_asm(usrc, uoff[nb], t0 * 2 + 32, ux + wv * kX + nb * 64);
+    }
+  };
+  // RAG: the run's 16 tokens out of the 9 words at and after its 4-byte boundary
+  auto shift_run = [&](UPieces& pu, int nb, uint32_t extra) {
+    uint32_t d[9];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) d[i] = pu[nb][i >> 2][i & 3];
+    d[8] = extra;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pu[nb][i >> 2][i & 3] = __builtin_amdgcn_alignbit(d[i + 1], d[i], ush[nb]);
+  };
+
+  // RAG, the vocabulary's last step: token V - 1 of each row once more, by its
+  // own load, into the tile (an array with an odd number of elements ends
+  // outside its whole words, and the word loads leave its last one out).
+  auto patch_last = [&](u32x4* ub, uint32_t* ux, int t0) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int pos = V - 1 - (t0 + g * 16);
+      const uint32_t row0 = (uoff[nb] + (ush[nb] >> 3)) / 2u - (uint32_t)g * 16u;  // the row's first element
+      const uint16_t last = U[row0 + (uint32_t)V - 1u];
+      const int at = pos + (int)(ush[nb] >> 4);  // its place, in 2-byte units from the run's 4-byte boundary
+      if (pos >= 0 && pos < 16) {
+        uint16_t* piece = reinterpret_cast<uint16_t*>(ub + wv * kU + (nb * 2 + (at >> 3)) * 64 + lane);
+        if (at >= 16) piece = reinterpret_cast<uint16_t*>(ux + wv * kX + nb * 64 + lane);
+        piece[at & 7] = last;
+      }
+    }
+    asm volatile("" ::: "memory");
   };
 
   // The vocabulary's last step when V % 64 != 0: with V % 8 == 0 every 8-token
   // piece of U lies wholly before V or wholly at or past it; the latter (their
   // loads read the next row, or zeros past the array) become bf16 -inf, so
   // those logits are -inf.
+  // RAG: token by token, the kept halves of a word from a shifted mask.
   auto mask_tail = [&](UPieces& pu, int t0) {
+    if constexpr (RAG) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int keep = min(max(V - (t0 + g * 16 + 2 * i), 0), 2);  // tokens of word i before V
+          const uint32_t m = (uint32_t)((1ull << (16 * keep)) - 1ull);
+          pu[nb][i >> 2][i & 3] = (pu[nb][i >> 2][i & 3] & m) | (0xFF80FF80u & ~m);
+        }
+      return;
+    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -1029,13 +1080,14 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     u32x4* wcur = (j & 1) ? w1 : w0;
     u32x4* wnext = (j & 1) ? w0 : w1;
     u32x4* ucur = (j & 1) ? ub1 : ub0;
+    uint32_t* xcur = (j & 1) ? ux1 : ux0;
     const bool more = t0 + 64 < tend;
     const bool more2 = t0 + 128 < tend;
     // this step's tiles are in LDS once at most the next step's U pieces
-    // (2 NB per lane, queued last) are outstanding; stores issued since only
-    // make the wait longer
+    // (kULoads * NB per lane, queued last) are outstanding; stores issued since
+    // only make the wait longer
     if (more && active)
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NB));
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads * NB));
     else
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     // the waits above order the tiles' arrival; a barrier with the usual
@@ -1044,17 +1096,26 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     lower_priority(step);
     if (more) issue_w(wnext, t0 + 64);
     if (active) {
+      if constexpr (RAG)
+        if (t0 + 64 > V) patch_last(ucur, xcur, t0);
       UPieces pu;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int h = 0; h < 2; ++h) pu[nb][h] = ucur[wv * kU + (nb * 2 + h) * 64 + lane];
+      uint32_t px[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) px[nb] = RAG ? xcur[wv * kX + nb * 64 + lane] : 0u;
       AFrags af;
       read_a(wcur, af);
       // the pieces are in registers before the loads two steps ahead overwrite
       // them (and no LDS read of the step comes after those loads)
       __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-      if (more2) issue_u(ucur, t0 + 128);
+      if (more2) issue_u(ucur, xcur, t0 + 128);
+      if constexpr (RAG) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) shift_run(pu, nb, px[nb]);
+      }
       if (t0 + 64 > V) mask_tail(pu, t0);
       f32x4 accs[NB][4];
 #pragma unroll
@@ -1070,8 +1131,8 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   };
   issue_w(w0, t0);
   if (active) {
-    issue_u(ub0, t0);
-    if (t0 + 64 < tend) issue_u(ub1, t0 + 64);
+    issue_u(ub0, ux0, t0);
+    if (t0 + 64 < tend) issue_u(ub1, ux1, t0 + 64);
   }
   for (;;) {
     if (!do_step(std::integral_constant<int, 0>{})) break;

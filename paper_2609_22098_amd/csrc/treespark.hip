@@ -148,7 +148,7 @@ struct Plan {
   int ks;
   int mode;     // kModeGreedy, kModeGumbel or kModeSeq (the kernels' mode)
   bool sample;  // T > 0: the merge takes lse of z/T and draws
-  bool lds;     // LDS-staged bf16 streaming kernel
+  EvalPath path;  // LDS-staged bf16 streaming kernel (aligned or ragged rows) or the register one
   int nblk;     // 64-token blocks of the vocabulary
   int blk_ld;   // row stride of the block table (nblk rounded up to 16)
   size_t off_m, off_s0, off_sT, off_z[2], off_g[2], off_blk;
@@ -170,10 +170,10 @@ int device_cus() {
 }
 
 // Resident blocks per CU of the streaming kernel for this plan (2 if unknown).
-int eval_blocks_per_cu(int dtype, int ks, int nb, int mode, bool store_z, bool lds, int block) {
+int eval_blocks_per_cu(int dtype, int ks, int nb, int mode, bool store_z, EvalPath path, int block) {
   static std::mutex mu;
-  static std::map<std::tuple<int, int, int, int, bool, bool, int>, int> cache;
-  const auto key = std::make_tuple(dtype, ks, nb, mode, store_z, lds, block);
+  static std::map<std::tuple<int, int, int, int, bool, EvalPath, int>, int> cache;
+  const auto key = std::make_tuple(dtype, ks, nb, mode, store_z, path, block);
   {
     std::lock_guard<std::mutex> lock(mu);
     const auto it = cache.find(key);
@@ -182,16 +182,16 @@ int eval_blocks_per_cu(int dtype, int ks, int nb, int mode, bool store_z, bool l
   int n = 0;
   if (dtype == TS_BF16) {
     switch (ks) {
-      case 1: n = eval_blocks_per_cu_t<uint16_t, 1>(nb, mode, store_z, lds, block); break;
-      case 2: n = eval_blocks_per_cu_t<uint16_t, 2>(nb, mode, store_z, lds, block); break;
-      case 4: n = eval_blocks_per_cu_t<uint16_t, 4>(nb, mode, store_z, lds, block); break;
-      default: n = eval_blocks_per_cu_t<uint16_t, 8>(nb, mode, store_z, lds, block); break;
+      case 1: n = eval_blocks_per_cu_t<uint16_t, 1>(nb, mode, store_z, path, block); break;
+      case 2: n = eval_blocks_per_cu_t<uint16_t, 2>(nb, mode, store_z, path, block); break;
+      case 4: n = eval_blocks_per_cu_t<uint16_t, 4>(nb, mode, store_z, path, block); break;
+      default: n = eval_blocks_per_cu_t<uint16_t, 8>(nb, mode, store_z, path, block); break;
     }
   } else {
     switch (ks) {
-      case 4: n = eval_blocks_per_cu_t<float, 4>(nb, mode, store_z, lds, block); break;
-      case 8: n = eval_blocks_per_cu_t<float, 8>(nb, mode, store_z, lds, block); break;
-      default: n = eval_blocks_per_cu_t<float, 16>(nb, mode, store_z, lds, block); break;
+      case 4: n = eval_blocks_per_cu_t<float, 4>(nb, mode, store_z, path, block); break;
+      case 8: n = eval_blocks_per_cu_t<float, 8>(nb, mode, store_z, path, block); break;
+      default: n = eval_blocks_per_cu_t<float, 16>(nb, mode, store_z, path, block); break;
     }
   }
   if (n <= 0) n = 2;
@@ -224,15 +224,16 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   pl.NB = (P >= 512 && !max_chunks) ? 2 : 1;
   if (store_z) pl.NB = 1;
   // the LDS kernel reads U and W2 as raw buffers: byte offsets under 2^31
-  pl.lds = d->dtype == TS_BF16 && d->V % 8 == 0 && !store_z &&
-           ((uint64_t)d->R * d->D + 1) * d->V * 2 + 64 < (1ull << 31) &&
-           (uint64_t)d->V * d->r * 2 < (1ull << 31);
+  const bool lds = d->dtype == TS_BF16 && !store_z && ((uint64_t)d->R * d->D + 1) * d->V * 2 + 64 < (1ull << 31) &&
+                   (uint64_t)d->V * d->r * 2 < (1ull << 31);
+  pl.path = !lds ? EvalPath::kRegisters : d->V % 8 == 0 ? EvalPath::kLds : EvalPath::kLdsRagged;
   pl.n_pblocks = (P + 16 * pl.NB - 1) / (16 * pl.NB);
   // waves per workgroup (each workgroup loads every W2 tile of its chunk
   // once): eight for the greedy LDS kernel with two blocks per wave at rank
-  // <= 64 (that kernel fits four waves per SIMD), else four
-  pl.wpg = pl.lds ? 4 : std::min(4, std::max(1, pl.n_pblocks));
-  if (pl.lds && pl.NB == 2 && pl.ks <= 2 && pl.mode == kModeGreedy) pl.wpg = 8;
+  // <= 64 (that kernel fits four waves per SIMD; with the ragged rows' extra
+  // pieces its LDS would leave one workgroup per CU), else four
+  pl.wpg = lds ? 4 : std::min(4, std::max(1, pl.n_pblocks));
+  if (pl.path == EvalPath::kLds && pl.NB == 2 && pl.ks <= 2 && pl.mode == kModeGreedy) pl.wpg = 8;
   pl.n_pgroups = (pl.n_pblocks + pl.wpg - 1) / pl.wpg;
   // Chunks: enough workgroups to fill every CU at the kernel's occupancy in
   // whole rounds (all workgroups of a round finish together), chunks of
@@ -242,7 +243,7 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
     vc = 256;
   } else {
     const int concurrent = device_cus() *
-        eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.lds, 64 * pl.wpg);
+        eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg);
     const int s_min = (d->V + 4095) / 4096;
     const int rounds = std::max(1, (pl.n_pgroups * s_min + concurrent - 1) / concurrent);
     // at most rounds * concurrent workgroups: a few more would take a round of their own
@@ -254,7 +255,7 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
 #endif
   vc = std::max(vc, (d->V + kMaxChunks - 1) / kMaxChunks);
   // the LDS kernel sums block masses over quads of steps: chunks of whole quads
-  const int quantum = pl.lds ? 256 : 64;
+  const int quantum = lds ? 256 : 64;
   vc = ((vc + quantum - 1) / quantum) * quantum;
   vc = std::min(std::max(vc, 256), 4096);
   pl.Vc = vc;
@@ -263,8 +264,8 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
 #ifdef TS_DEBUG_RUNS
   if (!sizing_only)
     fprintf(stderr, "[plan] P=%d NB=%d lds=%d wpg=%d n_pgroups=%d Vc=%d S=%d grid=%d bpc=%d cus=%d\n", P,
-            pl.NB, (int)pl.lds, pl.wpg, pl.n_pgroups, pl.Vc, pl.S, pl.S8 * pl.n_pgroups,
-            eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.lds, 64 * pl.wpg), device_cus());
+            pl.NB, (int)pl.path, pl.wpg, pl.n_pgroups, pl.Vc, pl.S, pl.S8 * pl.n_pgroups,
+            eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg), device_cus());
 #endif
   const size_t a = align256((size_t)std::max(P, 1) * pl.S * 4);
   const size_t a4 = align256((size_t)std::max(P, 1) * pl.S * 4 * kTopRuns);
@@ -304,16 +305,16 @@ void launch_eval(const ts_drafter* d, const ExpandParams& p, const Plan& pl, hip
   const int mode = pl.mode | (p.need_T && pl.mode != kModeGreedy ? kModeNeedT : 0);
   if (d->dtype == TS_BF16) {
     switch (pl.ks) {
-      case 1: launch_eval_t<uint16_t, 1>(p, pl.NB, mode, z, pl.lds, grid, block, s); break;
-      case 2: launch_eval_t<uint16_t, 2>(p, pl.NB, mode, z, pl.lds, grid, block, s); break;
-      case 4: launch_eval_t<uint16_t, 4>(p, pl.NB, mode, z, pl.lds, grid, block, s); break;
-      default: launch_eval_t<uint16_t, 8>(p, pl.NB, mode, z, pl.lds, grid, block, s); break;
+      case 1: launch_eval_t<uint16_t, 1>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
+      case 2: launch_eval_t<uint16_t, 2>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
+      case 4: launch_eval_t<uint16_t, 4>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
+      default: launch_eval_t<uint16_t, 8>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
     }
   } else {
     switch (pl.ks) {
-      case 4: launch_eval_t<float, 4>(p, pl.NB, mode, z, false, grid, block, s); break;
-      case 8: launch_eval_t<float, 8>(p, pl.NB, mode, z, false, grid, block, s); break;
-      default: launch_eval_t<float, 16>(p, pl.NB, mode, z, false, grid, block, s); break;
+      case 4: launch_eval_t<float, 4>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
+      case 8: launch_eval_t<float, 8>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
+      default: launch_eval_t<float, 16>(p, pl.NB, mode, z, pl.path, grid, block, s); break;
     }
   }
 }
