@@ -45,6 +45,20 @@ struct RunSummaryPtr {
   float* rest;
 };
 
+// How the vocabulary is cut into chunks: whole units of `unit` tokens (256,
+// or 64 where no quads of steps are summed), the first `longer` chunks one
+// unit longer than the others' `units`.  Chunks of one length would leave the
+// last units of a rounded-up length to fewer chunks than the launch has
+// workgroups for: 256 parents, V = 151936, r = 128 then ran 596 workgroups of
+// 1024 tokens where 768 fit the chip.  ts_expand with rounded-up lengths and
+// with these: that wave 58.4 and 54.7 us, 512 parents over V = 100003 74.4 and
+// 66.9, 128 parents at r = 256 75.3 and 69.4, the 2048-parent serving
+// frontier 100.9 and 97.4 (greedy), 300.9 and 289.2 (Gumbel), 146.9 and 145.5.
+struct ChunkMap {
+  int unit, units, longer;
+  __device__ __forceinline__ int begin(int c) const { return unit * (c * units + min(c, longer)); }
+};
+
 struct ExpandParams {
   const void* U;
   const void* E;
@@ -52,7 +66,7 @@ struct ExpandParams {
   int R, D, V, r;
   const ts_parent* parents;
   int P;
-  int Vc;         // tokens per chunk, multiple of 64
+  ChunkMap cm;    // chunks of the vocabulary, at most 4096 tokens each
   int S;          // number of chunks
   int n_pblocks;  // parent blocks of 16 * NB parents (one wave each)
   int wpg;        // waves (parent blocks) per workgroup
@@ -412,8 +426,10 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
   float m0[NB], s0[NB], sT[NB];
   RunTop zt[NB], gt[NB];
   BlkWindow bw[NB];
-  const int bfirst = chunk * (p.Vc >> 6);
-  const int blast = (min(chunk * p.Vc + p.Vc, V) - 1) >> 6;
+  const int tbeg = p.cm.begin(chunk);
+  const int tend = min(p.cm.begin(chunk + 1), V);
+  const int bfirst = tbeg >> 6;
+  const int blast = (tend - 1) >> 6;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     m0[nb] = kNegInf; s0[nb] = 0.0f; sT[nb] = 0.0f;
@@ -536,8 +552,6 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 
   // Steps alternate between two buffers of U values and W2 fragments: the
   // next step's loads are in flight while the current step computes.
-  const int tbeg = chunk * p.Vc;
-  const int tend = min(tbeg + p.Vc, V);
   URun<TE> ua[NB], ub[NB];
   FT aa[4][KS], ab[4][KS];
   int t0 = tbeg, step = 0;
@@ -796,8 +810,10 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   constexpr bool SUM0 = !SEQ || NT;
   constexpr bool SUMT = NT && !SEQ;
   const float cX = NT ? p.cT : kLog2e;  // scale of the block masses
-  const int bfirst = chunk * (p.Vc >> 6);
-  const int blast = (min(chunk * p.Vc + p.Vc, V) - 1) >> 6;
+  const int tbeg = p.cm.begin(chunk);
+  const int tend = min(p.cm.begin(chunk + 1), V);
+  const int bfirst = tbeg >> 6;
+  const int blast = (tend - 1) >> 6;
   // the vocabulary's last chunk may write its last window whole (the row is padded to 16 blocks)
   const int bstore = blast == p.nblk - 1 ? p.blk_ld - 1 : blast;
 #pragma unroll
@@ -1051,8 +1067,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     }
   };
 
-  const int tbeg = chunk * p.Vc;
-  const int tend = min(tbeg + p.Vc, V);
   // Issue priority falls as the wave walks its chunk (3 in the first quarter,
   // then 2, 1, 0), so that on a SIMD the waves that are behind are served
   // first.  With equal priorities the oldest wave wins every arbitration:

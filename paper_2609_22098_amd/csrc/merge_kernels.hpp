@@ -14,7 +14,8 @@ struct MergeParams {
   int R, D, V, r;
   const ts_parent* parents;
   int P;
-  int Vc, S;
+  ChunkMap cm;
+  int S;
   int K;
   float T, cT;
   int need_T;
@@ -251,7 +252,7 @@ __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* uro
     const bool live = b < nrun && tb + e < V;
     float rm = live ? kv : kNegInf;
     rm = row_max(rm);  // the run's 16 keys sit in one row of 16 lanes
-    mism += __popcll(__ballot(live && e == 0 && !__builtin_isnan(ex) && run_key(rm, (tb % p.Vc) >> 4) != ex));
+    mism += __popcll(__ballot(live && e == 0 && !__builtin_isnan(ex) && run_key(rm, run_of(ex)) != ex));
     const float th = kd ? thr[1] : thr[0];
     uint64_t mask = __ballot(live && kv >= th);
     while (mask) {
@@ -407,7 +408,7 @@ __device__ __forceinline__ float select_items_n(const MergeParams& p, const RunS
     const int off = base + __popcll(mask & lt);
     if (cand && off < kItemCap) {
       const int run = run_of(ev[i]);
-      L.item_t[off] = c * p.Vc + (run >> 2) * 64 + (run & 3) * 16;
+      L.item_t[off] = p.cm.begin(c) + (run >> 2) * 64 + (run & 3) * 16;
       L.item_k[off] = kind;
       L.item_e[off] = ev[i];
     }
@@ -896,8 +897,8 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
       float e;
       if (code < 0) {
         const int cc = -code - 1;
-        const int cbeg = cc * p.Vc;
-        const int nruns = ((min(cbeg + p.Vc, V) - cbeg + 63) / 64) * 4;
+        const int cbeg = p.cm.begin(cc);
+        const int nruns = ((min(p.cm.begin(cc + 1), V) - cbeg + 63) / 64) * 4;
         t = cbeg + (sub >> 2) * 64 + (sub & 3) * 16;
         e = nan;
         if (++sub == nruns) { sub = 0; ++it; }

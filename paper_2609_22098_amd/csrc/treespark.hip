@@ -144,7 +144,8 @@ PhiloxKeys philox_keys(uint64_t seed) {
 // ---------------------------------------------------------------- expansion plan
 
 struct Plan {
-  int NB, Vc, S, n_pblocks, wpg, n_pgroups, S8;
+  int NB, S, n_pblocks, wpg, n_pgroups, S8;
+  ChunkMap cm;
   int ks;
   int mode;     // kModeGreedy, kModeGumbel or kModeSeq (the kernels' mode)
   bool sample;  // T > 0: the merge takes lse of z/T and draws
@@ -209,8 +210,10 @@ static_assert(TS_MAX_V <= kMaxChunks * 4096, "the merge holds kMaxChunks chunks 
 // max_chunks: the most chunks the vocabulary allows (the plan of a launch
 // whose parent count is only bounded on the host: parallelism comes from the
 // chunks, and workgroups beyond the parents the device holds exit at once).
+// even_chunks: the fewer chunks that one rounded-up length takes, for scratch
+// that the plan with more of them does not fit.
 Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = false,
-               bool sizing_only = false, bool max_chunks = false) {
+               bool sizing_only = false, bool max_chunks = false, bool even_chunks = false) {
   Plan pl{};
   pl.sample = T > 0.0f && !store_z;
   pl.mode = !pl.sample ? kModeGreedy : sampler == TS_SAMPLER_SEQUENTIAL ? kModeSeq : kModeGumbel;
@@ -235,36 +238,36 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   pl.wpg = lds ? 4 : std::min(4, std::max(1, pl.n_pblocks));
   if (pl.path == EvalPath::kLds && pl.NB == 2 && pl.ks <= 2 && pl.mode == kModeGreedy) pl.wpg = 8;
   pl.n_pgroups = (pl.n_pblocks + pl.wpg - 1) / pl.wpg;
-  // Chunks: enough workgroups to fill every CU at the kernel's occupancy in
-  // whole rounds (all workgroups of a round finish together), chunks of
-  // 256..4096 tokens, at most kMaxChunks per parent.
-  int vc;
-  if (sizing_only || max_chunks) {
-    vc = 256;
-  } else {
+  // Chunks: as many workgroups as fit the chip at the kernel's occupancy, in
+  // whole rounds (a few more would take a round of their own), chunks of
+  // 256..4096 tokens, at most kMaxChunks per parent, their lengths within
+  // one unit of each other (ChunkMap).  Units of 256 tokens keep the quads of
+  // steps that sequential draws sum block masses over whole.
+  const int unit = lds && pl.mode == kModeSeq ? 256 : 64;
+  const int units = (d->V + unit - 1) / unit;
+  const int s_min = (units * unit + 4095) / 4096;
+  const int s_max = std::max(1, std::min((d->V + 255) / 256, kMaxChunks));
+  int S = s_max;
+  if (!sizing_only && !max_chunks) {
     const int concurrent = device_cus() *
         eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg);
-    const int s_min = (d->V + 4095) / 4096;
     const int rounds = std::max(1, (pl.n_pgroups * s_min + concurrent - 1) / concurrent);
-    // at most rounds * concurrent workgroups: a few more would take a round of their own
-    const int s_want = std::max(1, rounds * concurrent / pl.n_pgroups);
-    vc = (d->V + s_want - 1) / s_want;
+    S = std::max(1, rounds * concurrent / pl.n_pgroups);
+    if (even_chunks) {
+      // chunks of one rounded-up length: fewer of them
+      const int quantum = lds ? 256 : 64;
+      int vc = std::max((d->V + S - 1) / S, (d->V + kMaxChunks - 1) / kMaxChunks);
+      vc = std::min(std::max((vc + quantum - 1) / quantum * quantum, 256), 4096);
+      S = (d->V + vc - 1) / vc;
+    }
   }
-#ifdef TS_DEBUG_RUNS
-  if (!sizing_only && getenv("TS_VC")) vc = atoi(getenv("TS_VC"));
-#endif
-  vc = std::max(vc, (d->V + kMaxChunks - 1) / kMaxChunks);
-  // the LDS kernel sums block masses over quads of steps: chunks of whole quads
-  const int quantum = lds ? 256 : 64;
-  vc = ((vc + quantum - 1) / quantum) * quantum;
-  vc = std::min(std::max(vc, 256), 4096);
-  pl.Vc = vc;
-  pl.S = (d->V + vc - 1) / vc;
+  pl.S = std::min(std::max(S, s_min), std::max(s_max, s_min));
   pl.S8 = ((pl.S + 7) / 8) * 8;
+  pl.cm = ChunkMap{unit, units / pl.S, units % pl.S};
 #ifdef TS_DEBUG_RUNS
   if (!sizing_only)
-    fprintf(stderr, "[plan] P=%d NB=%d lds=%d wpg=%d n_pgroups=%d Vc=%d S=%d grid=%d bpc=%d cus=%d\n", P,
-            pl.NB, (int)pl.path, pl.wpg, pl.n_pgroups, pl.Vc, pl.S, pl.S8 * pl.n_pgroups,
+    fprintf(stderr, "[plan] P=%d NB=%d path=%d wpg=%d n_pgroups=%d S=%d grid=%d bpc=%d cus=%d\n", P,
+            pl.NB, (int)pl.path, pl.wpg, pl.n_pgroups, pl.S, pl.S8 * pl.n_pgroups,
             eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg), device_cus());
 #endif
   const size_t a = align256((size_t)std::max(P, 1) * pl.S * 4);
@@ -346,7 +349,7 @@ ExpandParams eval_params(const ts_drafter* d, const ts_parent* parents, int P, f
   p.R = d->R; p.D = d->D; p.V = d->V; p.r = d->r;
   p.parents = parents;
   p.P = P;
-  p.Vc = pl.Vc; p.S = pl.S;
+  p.cm = pl.cm; p.S = pl.S;
   p.n_pblocks = pl.n_pblocks; p.wpg = pl.wpg; p.n_pgroups = pl.n_pgroups;
   p.cT = T > 0.0f ? kLog2e / T : 0.0f;
   p.need_T = (T > 0.0f && T != 1.0f) ? 1 : 0;
@@ -369,9 +372,9 @@ ExpandParams eval_params(const ts_drafter* d, const ts_parent* parents, int P, f
 // the grids and the plan takes the most chunks.
 int32_t run_expand(const ts_drafter* d, const ts_parent* parents, int P, ts_calib calib, int k,
                    float T, uint64_t seed, int sampler, const ts_expand_out* out, char* ws,
-                   hipStream_t s, const int* P_dev = nullptr) {
+                   hipStream_t s, const int* P_dev = nullptr, bool even_chunks = false) {
   if (P == 0) return TS_OK;
-  const Plan pl = make_plan(d, P, T, sampler, false, false, P_dev != nullptr);
+  const Plan pl = make_plan(d, P, T, sampler, false, false, P_dev != nullptr, even_chunks);
   ExpandParams ep = eval_params(d, parents, P, T, seed, pl, ws, nullptr);
   ep.P_dev = P_dev;
   hipEvent_t* ev = reinterpret_cast<hipEvent_t*>(out->events);
@@ -384,7 +387,7 @@ int32_t run_expand(const ts_drafter* d, const ts_parent* parents, int P, ts_cali
   mp.R = d->R; mp.D = d->D; mp.V = d->V; mp.r = d->r;
   mp.parents = parents;
   mp.P = P;
-  mp.Vc = pl.Vc; mp.S = pl.S;
+  mp.cm = pl.cm; mp.S = pl.S;
   mp.K = k;
   mp.T = T; mp.cT = ep.cT; mp.need_T = ep.need_T;
   mp.calib_a = calib.a; mp.calib_b = calib.b;
@@ -864,13 +867,15 @@ int32_t ts_expand_noalloc(const ts_drafter* d, const ts_parent* parents, int32_t
   g_last_error.clear();
   int32_t rc = check_expand_args(d, parents, P, calib, k, T, sampler, out);
   if (rc != TS_OK || P == 0) return rc;
-  const size_t need = make_plan(d, P, T, sampler).bytes;
+  const size_t need = make_plan(d, P, T, sampler, false, false, false, true).bytes;
   if (need > (size_t)TS_NOALLOC_SCRATCH_BYTES)
     return fail(TS_EUNSUPPORTED, "this launch needs %zu bytes of scratch, more than the %u of ts_expand_noalloc",
                 need, TS_NOALLOC_SCRATCH_BYTES);
   char* scratch = nullptr;
   if ((rc = noalloc_scratch(&scratch)) != TS_OK) return rc;
-  return run_expand(d, parents, P, calib, k, T, seed, sampler, out, scratch, static_cast<hipStream_t>(stream));
+  const bool even = make_plan(d, P, T, sampler).bytes > (size_t)TS_NOALLOC_SCRATCH_BYTES;
+  return run_expand(d, parents, P, calib, k, T, seed, sampler, out, scratch, static_cast<hipStream_t>(stream), nullptr,
+                    even);
 }
 
 size_t ts_build_tree_workspace_size(const ts_drafter* d, int32_t N, int32_t K, float T) {
