@@ -96,10 +96,11 @@ __device__ __forceinline__ int launch_parents(const Params& p) {
   return p.P_dev ? min(*p.P_dev, p.P) : p.P;
 }
 
-// Sampling modes of a launch: greedy (T = 0), Gumbel-top-k draws, sequential draws.
+// Sampling modes of a launch: greedy (T = 0), Gumbel-top-k draws, sequential draws;
+// kModeStore (LDS kernel only) writes the logits and keeps nothing else.
 // The LDS streaming kernel also takes kModeNeedT in its mode (T != 1: a second
 // sum for log-sum-exp of z / T), so that both sums are computed together.
-enum : int { kModeGreedy = 0, kModeGumbel = 1, kModeSeq = 2, kModeNeedT = 4 };
+enum : int { kModeGreedy = 0, kModeGumbel = 1, kModeSeq = 2, kModeStore = 3, kModeNeedT = 4 };
 constexpr int kSegTokens = 4096;  // tokens per segment of the sequential draws
 constexpr int kBlkTokens = 64;    // tokens per block
 
@@ -489,6 +490,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
               if (tl + j < V) zo[tl + j] = v[j];
           }
         }
+        continue;  // the logits are all that is wanted
       }
       float bm = max2_med3(v[0], v[1]);
 #pragma unroll
@@ -570,6 +572,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
     t0 += 64; ++step;
   }
 
+  if constexpr (STORE_Z) return;
   // Combine the four lane groups of each parent (lanes n, n+16, n+32, n+48).
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
@@ -730,9 +733,10 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   __shared__ uint32_t ux1[RAG ? WPG * kX : 1];
   const int lane = threadIdx.x & 63;
   constexpr int BASE = MODE & 3;
-  constexpr bool SAMPLE = BASE != kModeGreedy;  // T > 0: lse of z/T and K draws
+  constexpr bool STORE = BASE == kModeStore;  // the logits themselves (verification recompute)
   constexpr bool GUMBEL = BASE == kModeGumbel;
   constexpr bool SEQ = BASE == kModeSeq;
+  constexpr bool SAMPLE = GUMBEL || SEQ;  // T > 0: lse of z/T and K draws
   constexpr bool NT = SAMPLE && (MODE & kModeNeedT) != 0;  // T != 1: a separate sum for z/T
   // the wave index is uniform: kept scalar, the LDS destinations of the
   // direct loads need no per-step readfirstlane
@@ -807,7 +811,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   float hw[NB][4];  // sequential draws: the open window's block log-masses, hw[k] = block 4k + g
   // sequential draws keep no sum of z / T, and at T = 1 no sum at all: the
   // merge takes those log-sum-exps from the block masses
-  constexpr bool SUM0 = !SEQ || NT;
+  constexpr bool SUM0 = !STORE && (!SEQ || NT);
   constexpr bool SUMT = NT && !SEQ;
   const float cX = NT ? p.cT : kLog2e;  // scale of the block masses
   const int tbeg = p.cm.begin(chunk);
@@ -987,6 +991,36 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     return bm;
   };
 
+  // STORE (the verification recompute; against the register kernel with its
+  // sums and 256 chunks, 64 rows of V = 151936, r = 64: 34 -> 31 us cold, 20
+  // -> 15 us over the levels of a walk): the run's 16 logits.  A whole step's stores are buffer stores that
+  // every wave issues in full (a lane without a parent has an offset past the
+  // buffer, which drops them): the waits of the following steps count on
+  // their number.  The vocabulary's last step, which nothing follows, stores
+  // token by token.
+  uint32_t zoff[NB];
+  const auto zdst = __builtin_amdgcn_make_buffer_rsrc(p.z_out, 0, STORE ? (int)((uint32_t)P * V * 4) : 0, kRawBufferFlags);
+  if constexpr (STORE) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      zoff[nb] = pidx[nb] < P ? ((uint32_t)pidx[nb] * (uint32_t)V + (uint32_t)g * 16u) * 4u : 0xFFFFFFC0u;
+  }
+  constexpr int kStores = STORE ? 4 * NB : 0;  // stores per whole step
+  auto store_run = [&](int nb, const f32x4 (&acc)[4], int t0) {
+    if (t0 + 64 <= V) {
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb) 
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[bb]), zdst, (int)zoff[nb],
+                                               t0 * 4 + 16 * bb, 0);
+    } else if (pidx[nb] < P) {
+      float* zo = p.z_out + (size_t)pidx[nb] * V;
+      const int tl = t0 + g * 16;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (tl + i < V) zo[tl + i] = acc[i >> 2][i & 3];
+    }
+  };
+
   // One 64-token step; j is the step's place in its quad (known at compile time).
   auto compute = [&](const AFrags& af, f32x4 (&accs)[NB][4], int t0, int step, auto jtag) {
     constexpr int j = decltype(jtag)::value;
@@ -1024,7 +1058,10 @@ void expand_eval_lds_kernel(const ExpandParams p) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       logits(af, nb, accs[nb]);
-      epilogue(nb, accs[nb]);
+      if constexpr (STORE)
+        store_run(nb, accs[nb], t0);
+      else
+        epilogue(nb, accs[nb]);
     }
   };
 
@@ -1098,10 +1135,12 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     const bool more = t0 + 64 < tend;
     const bool more2 = t0 + 128 < tend;
     // this step's tiles are in LDS once at most the next step's U pieces
-    // (kULoads * NB per lane, queued last) are outstanding; stores issued since
-    // only make the wait longer
-    if (more && active)
+    // (kULoads * NB per lane) are outstanding, and the previous step's logit
+    // stores, issued after them; block-table stores only make the wait longer
+    if (more && active && (kStores == 0 || step == 0))
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads * NB));
+    else if (more && active)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads * NB + kStores));
     else
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     // the waits above order the tiles' arrival; a barrier with the usual
@@ -1155,6 +1194,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     if (!do_step(std::integral_constant<int, 3>{})) break;
   }
   if (!active) return;
+  if constexpr (STORE) return;
 
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {

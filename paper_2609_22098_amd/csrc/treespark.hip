@@ -227,8 +227,10 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   pl.NB = (P >= 512 && !max_chunks) ? 2 : 1;
   if (store_z) pl.NB = 1;
   // the LDS kernel reads U and W2 as raw buffers: byte offsets under 2^31
-  const bool lds = d->dtype == TS_BF16 && !store_z && ((uint64_t)d->R * d->D + 1) * d->V * 2 + 64 < (1ull << 31) &&
-                   (uint64_t)d->V * d->r * 2 < (1ull << 31);
+  // (and the stored logits as one under 2^32)
+  const bool lds = d->dtype == TS_BF16 && ((uint64_t)d->R * d->D + 1) * d->V * 2 + 64 < (1ull << 31) &&
+                   (uint64_t)d->V * d->r * 2 < (1ull << 31) &&
+                   (!store_z || (uint64_t)P * d->V * 4 + 256 < (1ull << 32));
   pl.path = !lds ? EvalPath::kRegisters : d->V % 8 == 0 ? EvalPath::kLds : EvalPath::kLdsRagged;
   pl.n_pblocks = (P + 16 * pl.NB - 1) / (16 * pl.NB);
   // waves per workgroup (each workgroup loads every W2 tile of its chunk
@@ -246,7 +248,8 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   const int unit = lds && pl.mode == kModeSeq ? 256 : 64;
   const int units = (d->V + unit - 1) / unit;
   const int s_min = (units * unit + 4095) / 4096;
-  const int s_max = std::max(1, std::min((d->V + 255) / 256, kMaxChunks));
+  // the logit recompute leaves no partials: its chunks are not limited
+  const int s_max = std::max(1, std::min((d->V + 255) / 256, store_z && !sizing_only ? INT_MAX : kMaxChunks));
   int S = s_max;
   if (!sizing_only && !max_chunks) {
     const int concurrent = device_cus() *
@@ -298,8 +301,8 @@ RunSummaryPtr summary_ptr(char* ws, const size_t (&off)[2]) {
   return r;
 }
 
-size_t expand_ws_max(const ts_drafter* d, int Pmax, float T, bool store_z = false) {
-  return make_plan(d, std::max(Pmax, 1), T, TS_SAMPLER_GUMBEL, store_z, true).bytes;
+size_t expand_ws_max(const ts_drafter* d, int Pmax, float T) {
+  return make_plan(d, std::max(Pmax, 1), T, TS_SAMPLER_GUMBEL, false, true).bytes;
 }
 
 void launch_eval(const ts_drafter* d, const ExpandParams& p, const Plan& pl, hipStream_t s) {
@@ -342,6 +345,7 @@ void launch_merge(const ts_drafter* d, const MergeParams& p, const Plan& pl, hip
   }
 }
 
+// z_out: the logits are stored there and nothing is kept in ws (null).
 ExpandParams eval_params(const ts_drafter* d, const ts_parent* parents, int P, float T, uint64_t seed,
                          const Plan& pl, char* ws, float* z_out) {
   ExpandParams p{};
@@ -355,6 +359,8 @@ ExpandParams eval_params(const ts_drafter* d, const ts_parent* parents, int P, f
   p.need_T = (T > 0.0f && T != 1.0f) ? 1 : 0;
   p.hr = 60.0f / std::max(kLog2e, p.cT);
   p.keys = philox_keys(seed);
+  p.z_out = z_out;
+  if (z_out) return p;
   p.part_m = reinterpret_cast<float*>(ws + pl.off_m);
   p.part_s0 = reinterpret_cast<float*>(ws + pl.off_s0);
   p.part_sT = pl.sample ? reinterpret_cast<float*>(ws + pl.off_sT) : nullptr;
@@ -363,7 +369,6 @@ ExpandParams eval_params(const ts_drafter* d, const ts_parent* parents, int P, f
   p.nblk = pl.nblk;
   p.blk_ld = pl.blk_ld;
   if (pl.mode == kModeSeq) p.blk = reinterpret_cast<float*>(ws + pl.off_blk);
-  p.z_out = z_out;
   return p;
 }
 
@@ -693,7 +698,7 @@ const KidIndex& kid_index(const ts_tree* t) {
 }
 
 struct VerifyLayout {
-  size_t off_items, off_z, off_exp;
+  size_t off_items, off_z;
   size_t off_pa, off_zp, off_bp, off_cst, off_rec, off_sync, bytes;
   int max_chunks;
 };
@@ -719,11 +724,13 @@ struct FusedPlan {
 };
 // Polls of one wait before it gives up (a poll takes about a microsecond).
 constexpr int kFusedSpinLimit = 1 << 16;
+// Workgroups of a one-launch level that the device holds at once, the most
+// such a launch has (its slots beyond them are never used, nor cleared).
+long long fused_capacity(bool bf16) { return (long long)std::max(verify_fused_blocks_per_cu(bf16), 0) * device_cus(); }
 FusedPlan fused_plan(int V, int nitems, bool bf16) {
   FusedPlan fp{false, 0, 0};
-  const int bpc = verify_fused_blocks_per_cu(bf16);
-  if (nitems < 1 || bpc < 1) return fp;
-  const long long capacity = (long long)bpc * device_cus();
+  const long long capacity = fused_capacity(bf16);
+  if (nitems < 1 || capacity < 1) return fp;
   const int per_wg = verify_fused_quads(bf16) * kVChunkQuantum;
   const int cpi_min = (V + per_wg - 1) / per_wg;
   if (cpi_min > kFusedMaxCpi || (long long)nitems * cpi_min > std::min<long long>(capacity, kFusedMaxGrid)) return fp;
@@ -753,7 +760,6 @@ VerifyLayout verify_layout(const ts_drafter* d, int cap, float T) {
   } else {
     v.off_items = o; o += align256((size_t)d->R * sizeof(VerifyItem));
     v.off_z = o; o += align256((size_t)d->R * d->V * 4);
-    v.off_exp = o; o += expand_ws_max(d, d->R, T, true);
     v.max_chunks = (d->V + kVChunkQuantum - 1) / kVChunkQuantum;
     const size_t ic = (size_t)d->R * v.max_chunks;
     v.off_pa = o; o += align256(ic * sizeof(VPartA));
@@ -1243,7 +1249,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   auto launch_recompute = [&](int P) -> int32_t {
     const Plan pl = make_plan(d, P, T, TS_SAMPLER_GUMBEL, true);
     const ExpandParams ep =
-        eval_params(d, reinterpret_cast<const ts_parent*>(hs + hs_items), P, T, seed, pl, ws + vl.off_exp, zbuf);
+        eval_params(d, reinterpret_cast<const ts_parent*>(hs + hs_items), P, T, seed, pl, nullptr, zbuf);
     launch_eval(d, ep, pl, s);
     TS_HIP(hipGetLastError());
     return TS_OK;
@@ -1258,7 +1264,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   // the one-launch levels' slots and flag start the call at zero; each
   // launch tags its slot words with an epoch of its own
   uint64_t* dslots = reinterpret_cast<uint64_t*>(ws + vl.off_sync);
-  const size_t nslots = fused_slot_words(R);
+  const size_t nslots = std::min<size_t>(fused_slot_words(R), kSlotWords * fused_capacity(target_dtype == TS_BF16));
   int* derr = reinterpret_cast<int*>(dslots + nslots);
   const int nclear = (int)(nslots * 2 + 1);
   const bool bf16 = target_dtype == TS_BF16;

@@ -75,7 +75,8 @@ __device__ __forceinline__ float tquad_at(const f32x4& v, int e) { return v[e]; 
 // Tokens b .. b+3 of both rows (z only when zrow is set); tokens at or past
 // y1 read as -inf, which no maximum, sum or key takes up.  Quad loads when
 // the rows hold a multiple of 4 tokens (every quad of a chunk, a multiple of
-// 4 long, then lies wholly inside or outside it), token loads otherwise.
+// 4 long, then lies wholly inside or outside it); otherwise loads of any
+// alignment for whole quads, token loads for the one the row's end cuts.
 template <typename TT>
 __device__ __forceinline__ void load_quad_vec(const TT* trow, const float* zrow, int b, int y1,
                                               typename TQuad<TT>::type& t, f32x4& z) {
@@ -97,6 +98,11 @@ __device__ __forceinline__ void load_quad_vec(const TT* trow, const float* zrow,
 template <typename TT>
 __device__ __forceinline__ void load_quad_tok(const TT* trow, const float* zrow, int b, int y1,
                                               typename TQuad<TT>::type& t, f32x4& z) {
+  if (b + 4 <= y1) {
+    t = quad_words(trow + b);
+    z = zrow ? quad_words(zrow + b) : f32x4{kNegInf, kNegInf, kNegInf, kNegInf};
+    return;
+  }
   uint32_t tw[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
