@@ -385,8 +385,8 @@ int32_t ts_calib_fit(const float* x, const int32_t* y, const int32_t* sel, int32
 
 /*
  * ts_verify_set_mode: how ts_verify runs its T > 0 levels on the calling
- * thread.  TS_VERIFY_AUTO (the default): in one launch per level whenever
- * every workgroup of the level can be resident at once (the workgroups of an
+ * thread.  TS_VERIFY_AUTO (the default): in one launch for several levels whenever
+ * every workgroup of the launch can be resident at once (the workgroups of an
  * item wait for one another between the walk's steps), else through the
  * per-stage launches.  TS_VERIFY_STAGED: always through the per-stage
  * launches, which never wait on other workgroups; for callers that keep
@@ -402,11 +402,11 @@ int32_t ts_verify_set_mode(int32_t mode);
 
 /*
  * ts_verify_level_counts: how the T > 0 levels of ts_verify calls on the
- * calling thread ran.  *fused: levels run in one launch, each workgroup
+ * calling thread ran.  *fused: levels walked inside one launch, each workgroup
  * holding its chunk of the target and draft rows in registers (when every
- * workgroup of the level can be resident at once); *fallbacks: of those, the
- * levels run again through the per-stage launches because a wait between
- * workgroups ran out; *staged: levels run through the per-stage launches from
+ * workgroup of the launch can be resident at once; one launch may walk several
+ * levels); *fallbacks: of those, the levels run again through the per-stage
+ * launches because a wait between workgroups ran out; *staged: levels run through the per-stage launches from
  * the start (pass A, one launch per stage, resolve).  The counts are the
  * thread's totals since its first call (ts_release_thread_state keeps them).
  * Errors: NULL pointers.

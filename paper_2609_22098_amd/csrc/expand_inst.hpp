@@ -37,8 +37,8 @@ struct EvalKernels {
 template <typename TE, int KS>
 static void (*eval_kernel_for(int nb, int mode, bool store_z, EvalPath path, int block))(ExpandParams) {
   if constexpr (sizeof(TE) == 2) {
-    if (store_z && path == EvalPath::kLds) return expand_eval_lds_kernel<KS, 1, kModeStore, 4, false>;
-    if (store_z && path == EvalPath::kLdsRagged) return expand_eval_lds_kernel<KS, 1, kModeStore, 4, true>;
+    if (store_z && path == EvalPath::kLds) return logits_store_kernel<KS, false>;
+    if (store_z && path == EvalPath::kLdsRagged) return logits_store_kernel<KS, true>;
   }
   if (store_z) return expand_eval_kernel<TE, KS, 1, kModeGreedy, true>;
   if constexpr (sizeof(TE) == 2) {

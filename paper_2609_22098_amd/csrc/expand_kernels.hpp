@@ -96,11 +96,10 @@ __device__ __forceinline__ int launch_parents(const Params& p) {
   return p.P_dev ? min(*p.P_dev, p.P) : p.P;
 }
 
-// Sampling modes of a launch: greedy (T = 0), Gumbel-top-k draws, sequential draws;
-// kModeStore (LDS kernel only) writes the logits and keeps nothing else.
+// Sampling modes of a launch: greedy (T = 0), Gumbel-top-k draws, sequential draws.
 // The LDS streaming kernel also takes kModeNeedT in its mode (T != 1: a second
 // sum for log-sum-exp of z / T), so that both sums are computed together.
-enum : int { kModeGreedy = 0, kModeGumbel = 1, kModeSeq = 2, kModeStore = 3, kModeNeedT = 4 };
+enum : int { kModeGreedy = 0, kModeGumbel = 1, kModeSeq = 2, kModeNeedT = 4 };
 constexpr int kSegTokens = 4096;  // tokens per segment of the sequential draws
 constexpr int kBlkTokens = 64;    // tokens per block
 
@@ -733,10 +732,9 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   __shared__ uint32_t ux1[RAG ? WPG * kX : 1];
   const int lane = threadIdx.x & 63;
   constexpr int BASE = MODE & 3;
-  constexpr bool STORE = BASE == kModeStore;  // the logits themselves (verification recompute)
+  constexpr bool SAMPLE = BASE != kModeGreedy;  // T > 0: lse of z/T and K draws
   constexpr bool GUMBEL = BASE == kModeGumbel;
   constexpr bool SEQ = BASE == kModeSeq;
-  constexpr bool SAMPLE = GUMBEL || SEQ;  // T > 0: lse of z/T and K draws
   constexpr bool NT = SAMPLE && (MODE & kModeNeedT) != 0;  // T != 1: a separate sum for z/T
   // the wave index is uniform: kept scalar, the LDS destinations of the
   // direct loads need no per-step readfirstlane
@@ -811,7 +809,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   float hw[NB][4];  // sequential draws: the open window's block log-masses, hw[k] = block 4k + g
   // sequential draws keep no sum of z / T, and at T = 1 no sum at all: the
   // merge takes those log-sum-exps from the block masses
-  constexpr bool SUM0 = !STORE && (!SEQ || NT);
+  constexpr bool SUM0 = !SEQ || NT;
   constexpr bool SUMT = NT && !SEQ;
   const float cX = NT ? p.cT : kLog2e;  // scale of the block masses
   const int tbeg = p.cm.begin(chunk);
@@ -991,36 +989,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     return bm;
   };
 
-  // STORE (the verification recompute; against the register kernel with its
-  // sums and 256 chunks, 64 rows of V = 151936, r = 64: 34 -> 31 us cold, 20
-  // -> 15 us over the levels of a walk): the run's 16 logits.  A whole step's stores are buffer stores that
-  // every wave issues in full (a lane without a parent has an offset past the
-  // buffer, which drops them): the waits of the following steps count on
-  // their number.  The vocabulary's last step, which nothing follows, stores
-  // token by token.
-  uint32_t zoff[NB];
-  const auto zdst = __builtin_amdgcn_make_buffer_rsrc(p.z_out, 0, STORE ? (int)((uint32_t)P * V * 4) : 0, kRawBufferFlags);
-  if constexpr (STORE) {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-      zoff[nb] = pidx[nb] < P ? ((uint32_t)pidx[nb] * (uint32_t)V + (uint32_t)g * 16u) * 4u : 0xFFFFFFC0u;
-  }
-  constexpr int kStores = STORE ? 4 * NB : 0;  // stores per whole step
-  auto store_run = [&](int nb, const f32x4 (&acc)[4], int t0) {
-    if (t0 + 64 <= V) {
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) 
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[bb]), zdst, (int)zoff[nb],
-                                               t0 * 4 + 16 * bb, 0);
-    } else if (pidx[nb] < P) {
-      float* zo = p.z_out + (size_t)pidx[nb] * V;
-      const int tl = t0 + g * 16;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (tl + i < V) zo[tl + i] = acc[i >> 2][i & 3];
-    }
-  };
-
   // One 64-token step; j is the step's place in its quad (known at compile time).
   auto compute = [&](const AFrags& af, f32x4 (&accs)[NB][4], int t0, int step, auto jtag) {
     constexpr int j = decltype(jtag)::value;
@@ -1058,10 +1026,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       logits(af, nb, accs[nb]);
-      if constexpr (STORE)
-        store_run(nb, accs[nb], t0);
-      else
-        epilogue(nb, accs[nb]);
+      epilogue(nb, accs[nb]);
     }
   };
 
@@ -1135,12 +1100,10 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     const bool more = t0 + 64 < tend;
     const bool more2 = t0 + 128 < tend;
     // this step's tiles are in LDS once at most the next step's U pieces
-    // (kULoads * NB per lane) are outstanding, and the previous step's logit
-    // stores, issued after them; block-table stores only make the wait longer
-    if (more && active && (kStores == 0 || step == 0))
+    // (kULoads * NB per lane, queued last) are outstanding; stores issued since
+    // only make the wait longer
+    if (more && active)
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads * NB));
-    else if (more && active)
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads * NB + kStores));
     else
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     // the waits above order the tiles' arrival; a barrier with the usual
@@ -1194,7 +1157,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     if (!do_step(std::integral_constant<int, 3>{})) break;
   }
   if (!active) return;
-  if constexpr (STORE) return;
 
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
@@ -1224,6 +1186,186 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       top_store(p.zs, o, zc);
       if constexpr (GUMBEL) top_store(p.gs, o, gc);
     }
+  }
+}
+
+// The logits themselves, z[p][y] for the parents of a launch (verification
+// recompute), bf16.  Bound by memory: a row costs its U row (2 V bytes), the
+// logits written (4 V) and a share of W2.  The operands are the streaming
+// pass's with their roles swapped (E rows as A, W2 rows as B; the matrix core
+// gives the same values bit for bit), and column n of block bb is token 4 n +
+// bb of the step: a lane then holds four consecutive tokens of four parents,
+// and a store instruction writes 256 consecutive bytes of each of four rows.
+// With the streaming pass's layout (16 tokens of one parent per lane) a store
+// wrote 16-byte pieces of 64 lines; some 140 rows of V = 151936 (150 MB) took
+// 62 us instead of 35.  U and W2 are staged as in the streaming pass, the U
+// pieces so that the four reads of a step meet no bank conflict: piece k (8
+// tokens) of parent 4 g + e is at e * 32 + g * 8 + k.  RAG: as there.
+template <int KS, bool RAG>
+__global__ __launch_bounds__(256) void logits_store_kernel(const ExpandParams p) {
+  typedef Frag<uint16_t> F;
+  typedef typename F::type FT;
+  constexpr int kW = 4 * KS * 64;                // 16-byte pieces of a W2 tile
+  constexpr int kU = RAG ? 128 * 4 + 64 : 128 * 4;  // words of one wave's U tile (RAG: and of the rows' extra words)
+  constexpr int kULoads = RAG ? 3 : 2;
+  __shared__ __attribute__((aligned(16))) u32x4 w0[kW];
+  __shared__ __attribute__((aligned(16))) u32x4 w1[kW];
+  __shared__ __attribute__((aligned(16))) uint32_t ub0[4 * kU];
+  __shared__ __attribute__((aligned(16))) uint32_t ub1[4 * kU];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int b = blockIdx.x;
+  const int kx = b >> 3;
+  const int chunk = (b & 7) + 8 * (kx / p.n_pgroups);
+  const int pgroup = kx % p.n_pgroups;
+  if (chunk >= p.S) return;  // uniform over the workgroup
+  const int P = p.P, V = p.V, r = p.r;
+  const int p0 = (pgroup * 4 + wv) * 16;  // the wave's first parent
+  const bool active = p0 < P;             // idle waves still load W2 and join the barriers
+  const uint16_t* U = static_cast<const uint16_t*>(p.U);
+
+  // parent n of the wave: its token and U row
+  int tok = 0, row = 0;
+  if (p0 + n < P) {
+    const ts_parent par = p.parents[p0 + n];
+    if (par.token >= 0 && par.token < V && par.depth >= 0 && par.depth < p.D && par.request >= 0 && par.request < p.R) {
+      tok = par.token;
+      row = par.request * p.D + par.depth;
+    }
+  }
+  FT efrag[KS];
+  const uint16_t* erow = static_cast<const uint16_t*>(p.E) + (size_t)tok * r;
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) efrag[kk] = F::load(erow, kk * F::kPerStep, g);
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(efrag[kk]));  // resident before the first queued load
+  // byte offsets: of the lane's two U pieces, of its extra word (RAG), of its
+  // four output runs (past the buffer for a row that is not there)
+  uint32_t uoff[2], xoff = 0, zoff[4], ush[4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int q = ((lane >> 3) & 3) * 4 + 2 * h + (lane >> 5);
+    const uint32_t first = (uint32_t)__shfl(row, q, 64) * (uint32_t)V * 2u;
+    uoff[h] = (RAG ? first & ~3u : first) + (uint32_t)(lane & 7) * 16u;
+  }
+  if constexpr (RAG) xoff = ((uint32_t)row * (uint32_t)V * 2u & ~3u) + 128u;
+  uint32_t rowe[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int q = g * 4 + e;
+    rowe[e] = (uint32_t)__shfl(row, q, 64);
+    ush[e] = RAG ? (rowe[e] * (uint32_t)V & 1u) << 4 : 0u;
+    zoff[e] = p0 + q < P ? ((uint32_t)(p0 + q) * (uint32_t)V + 4u * n) * 4u : 0xFFFFFFC0u;
+  }
+  uint32_t woff[KS];
+#pragma unroll
+  for (int j = 0; j < KS; ++j) {
+    const int bb = (wv * KS + j) / KS, kk = (wv * KS + j) % KS;
+    woff[j] = (uint32_t)(((4 * n + bb) * r + kk * 32 + g * 8) * 2);
+  }
+  const u32x4 wsrc = raw_rsrc(p.W2, (uint32_t)V * r * 2);
+  const u32x4 usrc = raw_rsrc(p.U, (uint32_t)p.R * p.D * V * 2 & (RAG ? ~3u : ~0u));
+  const auto zdst = __builtin_amdgcn_make_buffer_rsrc(p.z_out, 0, (int)((uint32_t)P * V * 4), kRawBufferFlags);
+  auto issue_w = [&](u32x4* wb, int t0) {
+#pragma unroll
+    for (int j = 0; j < KS; ++j) lds_buf16_asm(wsrc, woff[j], t0 * r * 2, wb + (wv * KS + j) * 64);
+  };
+  auto issue_u = [&](uint32_t* ub, int t0) {
+    uint32_t* mine = ub + wv * kU;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) lds_buf16_asm(usrc, uoff[h], t0 * 2, reinterpret_cast<const u32x4*>(mine) + h * 64);
+    if constexpr (RAG) lds_buf4_asm(usrc, xoff, t0 * 2, mine + 512);
+  };
+
+  const int tbeg = p.cm.begin(chunk);
+  const int tend = min(p.cm.begin(chunk + 1), V);
+  int t0 = tbeg;
+  bool first = true;
+  // as the streaming pass's step: U two steps ahead, W2 one
+  auto do_step = [&](u32x4* wcur, u32x4* wnext, uint32_t* ucur) -> bool {
+    const bool more = t0 + 64 < tend;
+    const bool more2 = t0 + 128 < tend;
+    // the step's tiles have landed once only the next step's U pieces and, but
+    // for the first step, the previous step's four stores are outstanding
+    // (issued after the tiles, and by every active wave)
+    if (more && active && first)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads));
+    else if (more && active)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(kULoads + 4));
+    else
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    first = false;
+    asm volatile("s_barrier" ::: "memory");
+    if (more) issue_w(wnext, t0 + 64);
+    if (active) {
+      const uint32_t* mine = ucur + wv * kU;
+      uint2 u[4];
+      uint32_t x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        u[e] = reinterpret_cast<const uint2*>(mine)[(e * 32 + g * 8) * 2 + n];
+        x[e] = RAG ? mine[n < 15 ? (e * 32 + g * 8) * 4 + 2 * n + 2 : 512 + g * 4 + e] : 0u;
+      }
+      FT wf[4][KS];
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb)
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) wf[bb][kk] = __builtin_bit_cast(FT, wcur[(bb * KS + kk) * 64 + lane]);
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): read before the pieces two steps ahead overwrite them
+      if (more2) issue_u(ucur, t0 + 128);
+      f32x4 acc[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint2 d = u[e];
+        if constexpr (RAG)
+          d = uint2{__builtin_amdgcn_alignbit(d.y, d.x, ush[e]), __builtin_amdgcn_alignbit(x[e], d.y, ush[e])};
+        acc[0][e] = __uint_as_float(d.x << 16);
+        acc[1][e] = __uint_as_float(d.x & 0xFFFF0000u);
+        acc[2][e] = __uint_as_float(d.y << 16);
+        acc[3][e] = __uint_as_float(d.y & 0xFFFF0000u);
+      }
+      if (RAG && t0 + 64 > V) {
+        // the vocabulary's last token by its own load: an array with an odd
+        // number of elements ends outside the whole words that were loaded
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float last = bf16_to_f32(U[rowe[e] * (uint32_t)V + (uint32_t)V - 1u]);
+#pragma unroll
+          for (int bb = 0; bb < 4; ++bb)
+            if (t0 + 4 * n + bb == V - 1) acc[bb][e] = last;
+        }
+      }
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+        for (int bb = 0; bb < 4; ++bb) acc[bb] = F::mma(efrag[kk], wf[bb][kk], acc[bb]);
+      if (t0 + 64 <= V) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          __builtin_amdgcn_raw_buffer_store_b128(
+              __builtin_bit_cast(u32x4, f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]}), zdst, (int)zoff[e], t0 * 4, 0);
+      } else {  // the vocabulary's last step
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int bb = 0; bb < 4; ++bb)
+            if (p0 + g * 4 + e < P && t0 + 4 * n + bb < V)
+              p.z_out[(size_t)(p0 + g * 4 + e) * V + t0 + 4 * n + bb] = acc[bb][e];
+      }
+    }
+    if (!more) return false;
+    t0 = __builtin_amdgcn_readfirstlane(t0 + 64);
+    return true;
+  };
+  issue_w(w0, t0);
+  if (active) {
+    issue_u(ub0, t0);
+    if (t0 + 64 < tend) issue_u(ub1, t0 + 64);
+  }
+  for (;;) {
+    if (!do_step(w0, w1, ub0)) break;
+    if (!do_step(w1, w0, ub1)) break;
   }
 }
 

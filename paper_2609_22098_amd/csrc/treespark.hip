@@ -679,27 +679,32 @@ const KidIndex& kid_index(const ts_tree* t) {
   thread_local KidIndex k;
   const int R = t->R, cap = t->cap;
   k.cap = cap;
-  k.off.assign((size_t)R * (cap + 1), 0);
+  k.off.resize((size_t)R * (cap + 1));
   k.list.resize((size_t)R * cap);
   for (int q = 0; q < R; ++q) {
     const int n = t->n[q];
-    int* off = k.off.data() + (size_t)q * (cap + 1);
+    int* off = k.off.data() + (size_t)q * (cap + 1);  // only entries 0 .. n + 1 are ever read
+    std::fill(off, off + n + 2, 0);
     const int32_t* par = t->parent + (size_t)q * cap;
     for (int i = 1; i <= n; ++i) ++off[par[i] + 1];
-    for (int p = 0; p < cap; ++p) off[p + 1] += off[p];
+    for (int p = 0; p <= n; ++p) off[p + 1] += off[p];
     // fill in increasing id order, which is creation order; off[p] ends at
     // the start of node p + 1 and is moved back afterwards
     int* list = k.list.data() + (size_t)q * cap;
     for (int i = 1; i <= n; ++i) list[off[par[i]]++] = i;
-    for (int p = cap; p > 0; --p) off[p] = off[p - 1];
+    for (int p = n + 1; p > 0; --p) off[p] = off[p - 1];
     off[0] = 0;
   }
   return k;
 }
 
 struct VerifyLayout {
-  size_t off_items, off_z;
-  size_t off_pa, off_zp, off_bp, off_cst, off_rec, off_sync, bytes;
+  size_t off_pa, off_zp, off_bp, off_cst, off_rec, off_sync;
+  // the logit rows of a round's nodes, the parents they are recomputed from
+  // and the nodes' items and children (last: their count follows the workspace)
+  size_t off_z, off_par, off_items;
+  int zrows, nodes;
+  size_t bytes;
   int max_chunks;
 };
 
@@ -752,14 +757,28 @@ size_t fused_slot_words(int R) {
   return (size_t)kSlotWords * (size_t)std::min<long long>((long long)R * kFusedMaxCpi, kFusedMaxGrid);
 }
 
-VerifyLayout verify_layout(const ts_drafter* d, int cap, float T) {
+// Logit rows a round of the T > 0 walk recomputes at most: those of the nodes
+// where the walks stand (at most R) and, with them, of nodes below that the
+// walks may reach, which a launch then goes on to by itself.  A row costs its
+// U row and the logits written, 6 V bytes (bf16), a round more about 35 us
+// (a recompute, a launch, the host's turn around), in which the chip moves
+// some 150 MB.
+constexpr size_t kAheadBytes = 144u << 20;
+constexpr int kAheadRows = 4096;
+int verify_rows(const ts_drafter* d, int cap) {
+  const long long nodes = (long long)d->R * std::max(cap - 1, 1);
+  const long long ahead = std::min<long long>(kAheadRows, (long long)(kAheadBytes / ((size_t)d->V * 6)));
+  return (int)std::max<long long>(d->R, std::min(nodes, ahead));
+}
+
+// zrows: logit rows (at least R); a workspace that holds fewer than
+// verify_rows takes as many as fit.
+VerifyLayout verify_layout(const ts_drafter* d, float T, int zrows) {
   VerifyLayout v{};
   size_t o = 0;
   if (T == 0.0f) {
     o = 256;  // the greedy walk works in the pinned staging buffer; 0 would mean an error
   } else {
-    v.off_items = o; o += align256((size_t)d->R * sizeof(VerifyItem));
-    v.off_z = o; o += align256((size_t)d->R * d->V * 4);
     v.max_chunks = (d->V + kVChunkQuantum - 1) / kVChunkQuantum;
     const size_t ic = (size_t)d->R * v.max_chunks;
     v.off_pa = o; o += align256(ic * sizeof(VPartA));
@@ -767,10 +786,53 @@ VerifyLayout verify_layout(const ts_drafter* d, int cap, float T) {
     v.off_bp = o; o += align256(ic * sizeof(VBonusPart));
     v.off_cst = o; o += align256((size_t)d->R * sizeof(VConst));
     v.off_rec = o; o += align256((size_t)d->R * TS_MAX_K * sizeof(VRec));
-    v.off_sync = o; o += align256(fused_slot_words(d->R) * 8 + 4);
+    v.off_sync = o; o += align256(fused_slot_words(d->R) * 8 + 16);
+    v.zrows = zrows;
+    v.nodes = zrows + d->R;  // and the walks that stand at nodes without children
+    v.off_z = o; o += align256((size_t)zrows * d->V * 4);
+    v.off_par = o; o += align256((size_t)zrows * sizeof(ts_parent));
+    v.off_items = o; o += align256((size_t)v.nodes * (sizeof(VerifyItem) + sizeof(VerifyNext)));
   }
   v.bytes = o;
   return v;
+}
+VerifyLayout verify_layout_for(const ts_drafter* d, int cap, float T, size_t have) {
+  int lo = d->R, hi = verify_rows(d, cap);  // the most rows that fit, at least R
+  VerifyLayout v = verify_layout(d, T, hi);
+  if (v.bytes <= have || T == 0.0f) return v;
+  while (lo < hi) {
+    const int mid = lo + (hi - lo + 1) / 2;
+    if (verify_layout(d, T, mid).bytes <= have) lo = mid; else hi = mid - 1;
+  }
+  return verify_layout(d, T, lo);
+}
+
+// Waits until every item of a one-launch round has its result words in pinned
+// memory.  Polling them spares the runtime's report of the launch's end
+// between rounds (64 requests, V = 100003: 157 us against 148).  *failed: a
+// wait between the launch's workgroups ran out; the stream is then idle.
+// After 20 ms, more than any round takes, the wait goes through the runtime,
+// which reports a failed launch.
+int32_t wait_round(const uint64_t* done, int words, uint32_t epoch, const volatile int32_t* herr, hipStream_t s,
+                   bool* failed) {
+  const auto t0 = std::chrono::steady_clock::now();
+  bool slow = false;
+  int i = 0;
+  for (unsigned n = 1; i < words && *herr == 0 && !slow; ++n) {
+    const uint64_t w = __atomic_load_n(done + i, __ATOMIC_ACQUIRE);
+    if ((uint32_t)(w >> 32) == epoch) {
+      ++i;
+      continue;
+    }
+    slow = (n & 1023) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(20);
+  }
+  *failed = false;
+  if (i == words) return TS_OK;
+  TS_HIP(hipStreamSynchronize(s));
+  *failed = *herr != 0;
+  for (; i < words && !*failed; ++i)
+    if ((uint32_t)(done[i] >> 32) != epoch) return fail(TS_EINTERNAL, "verification word %d has no result", i);
+  return TS_OK;
 }
 
 // Host checks shared by ts_expand and ts_expand_noalloc.
@@ -1111,7 +1173,7 @@ int32_t ts_build_tree(const ts_drafter* d, const int32_t* anchor, const float* t
 
 size_t ts_verify_workspace_size(const ts_drafter* d, int32_t cap, float T) {
   if (check_drafter(d) != TS_OK || cap < 1 || !(T >= 0.0f)) return 0;
-  return verify_layout(d, cap, T).bytes;
+  return verify_layout(d, T, verify_rows(d, cap)).bytes;
 }
 
 int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, int32_t target_dtype,
@@ -1141,7 +1203,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     if (tree->token[(size_t)q * cap] < 0 || tree->token[(size_t)q * cap] >= V)
       return fail(TS_EINVAL, "root token of request %d outside [0, V)", q);
   }
-  const VerifyLayout vl = verify_layout(d, cap, T);
+  const VerifyLayout vl = verify_layout_for(d, cap, T, workspace ? workspace_bytes : 0);
   if (!workspace || workspace_bytes < vl.bytes)
     return fail(TS_ENOSPACE, "workspace %zu bytes < %zu needed", workspace_bytes, vl.bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1221,96 +1283,110 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     return TS_OK;
   }
 
-  // T > 0: one level of the walk per iteration, batched over the requests still walking.
-  VerifyItem* ditems = reinterpret_cast<VerifyItem*>(ws + vl.off_items);
+  // T > 0: rounds over the requests still walking.  A round recomputes the
+  // logits of the nodes with children where the walks stand, and of as many
+  // such nodes below them as fit; then one launch walks every request from
+  // node to node until it ends or reaches a node without logits.  (Per-stage
+  // launches take one level a round.)  The host goes on as soon as it has seen
+  // every item's result in pinned memory.
   float* zbuf = reinterpret_cast<float*>(ws + vl.off_z);
   const PhiloxKeys keys = philox_keys(seed);
+  const bool bf16 = target_dtype == TS_BF16;
   std::vector<int> cur(R, 0), active(R);
   for (int q = 0; q < R; ++q) active[q] = q;
-  std::vector<VerifyItem> items;
-  std::vector<ts_parent> zpar;
   char* hs = nullptr;
-  const size_t hs_items = align256((size_t)R * sizeof(VerifyItem));
-  const size_t hs_par = align256((size_t)R * sizeof(ts_parent));
+  const size_t hs_par = align256((size_t)vl.zrows * sizeof(ts_parent));
+  const size_t hs_nodes = align256((size_t)vl.nodes * (sizeof(VerifyItem) + sizeof(VerifyNext)));
   const size_t hs_res = align256((size_t)R * sizeof(VerifyResult));
-  const size_t hs_next = align256((size_t)R * sizeof(VerifyNext));
-  if ((rc = host_stage(hs_items + hs_par + hs_res + hs_next + 256, &hs)) != TS_OK) return rc;
-  // The first level's logit recompute is queued first: its rows are the roots
-  // of the trees that have children (n > 0), in request order, which the
-  // level loop below assigns the same way; the child index and the level's
-  // items are built while it runs.
-  int first_rows = 0;
-  for (int q = 0; q < R; ++q) {
-    if (tree->n[q] <= 0) continue;
-    const size_t o = (size_t)q * cap;
-    reinterpret_cast<ts_parent*>(hs + hs_items)[first_rows++] =
-        ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]};
-  }
-  auto launch_recompute = [&](int P) -> int32_t {
-    const Plan pl = make_plan(d, P, T, TS_SAMPLER_GUMBEL, true);
-    const ExpandParams ep =
-        eval_params(d, reinterpret_cast<const ts_parent*>(hs + hs_items), P, T, seed, pl, nullptr, zbuf);
-    launch_eval(d, ep, pl, s);
-    TS_HIP(hipGetLastError());
-    return TS_OK;
-  };
-  if (first_rows > 0 && (rc = launch_recompute(first_rows)) != TS_OK) return rc;
+  const size_t hs_done = align256((size_t)R * kDoneWords * 8);
+  if ((rc = host_stage(hs_par + hs_nodes + hs_res + hs_done + 256, &hs)) != TS_OK) return rc;
+  ts_parent* hpar = reinterpret_cast<ts_parent*>(hs);
+  VerifyItem* hitem = reinterpret_cast<VerifyItem*>(hs + hs_par);  // a round's children records follow its items
+  VerifyResult* res = reinterpret_cast<VerifyResult*>(hs + hs_par + hs_nodes);
+  uint64_t* done = reinterpret_cast<uint64_t*>(hs + hs_par + hs_nodes + hs_res);
+  volatile int32_t* herr = reinterpret_cast<volatile int32_t*>(hs + hs_par + hs_nodes + hs_res + hs_done);
   // children of every node in creation order (= draw order)
   const KidIndex& kids = kid_index(tree);
-  bool first_level = true;
-  const VerifyResult* res = reinterpret_cast<const VerifyResult*>(hs + hs_items + hs_par);
-  VerifyNext* hnext = reinterpret_cast<VerifyNext*>(hs + hs_items + hs_par + hs_res);
-  volatile int32_t* herr = reinterpret_cast<volatile int32_t*>(hs + hs_items + hs_par + hs_res + hs_next);
   // the one-launch levels' slots and flag start the call at zero; each
-  // launch tags its slot words with an epoch of its own
+  // level of a launch tags its slot words with an epoch of its own
   uint64_t* dslots = reinterpret_cast<uint64_t*>(ws + vl.off_sync);
-  const size_t nslots = std::min<size_t>(fused_slot_words(R), kSlotWords * fused_capacity(target_dtype == TS_BF16));
+  const size_t nslots = std::min<size_t>(fused_slot_words(R), 2 * kSlotWords * fused_capacity(bf16));
   int* derr = reinterpret_cast<int*>(dslots + nslots);
-  const int nclear = (int)(nslots * 2 + 1);
-  const bool bf16 = target_dtype == TS_BF16;
-  uint32_t epoch = 0;
-  launch_verify_clear(reinterpret_cast<int*>(dslots), nclear, s);
-  TS_HIP(hipGetLastError());
+  size_t clear = nslots * 8 + 4;  // bytes to clear before the first launch
+  uint32_t epoch = 1;
+  std::vector<int> next, nodes, node_at((size_t)R * cap, kNextHost);
   while (!active.empty()) {
-    items.clear();
-    zpar.clear();
-    for (int q : active) {
-      const size_t o = (size_t)q * cap + cur[q];
+    const int ni = (int)active.size();
+    const FusedPlan fp = thread_state().verify_mode == TS_VERIFY_STAGED ? FusedPlan{false, 0, 0}
+                                                                          : fused_plan(V, ni, bf16);
+    // a launch that goes on to further nodes needs both halves of its slots
+    const bool ahead = fp.ok && (size_t)2 * ni * fp.cpi * kSlotWords <= nslots;
+    // the round's nodes: where the walks stand, then those below with
+    // children, breadth first; the rows of those with children in that order
+    nodes.clear();
+    int nz = 0;
+    auto add_node = [&](int q, int node) {
+      const size_t o = (size_t)q * cap + node;
+      node_at[o] = (int)nodes.size();
+      nodes.push_back((int)o);
+      if (kids.count(q, node) > 0) hpar[nz++] = ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]};
+    };
+    for (int q : active) add_node(q, cur[q]);
+    for (size_t i = 0; ahead && i < nodes.size() && nz < vl.zrows; ++i) {
+      const int q = nodes[i] / cap, p = nodes[i] % cap;
+      const int* ch = kids.first(q, p);
+      for (int j = 0, m = std::min(kids.count(q, p), TS_MAX_K); j < m && nz < vl.zrows; ++j)
+        if (kids.count(q, ch[j]) > 0) add_node(q, ch[j]);
+    }
+    const int nn = (int)nodes.size();
+    // Every workgroup of the recompute reads all of its rows' parents: they
+    // are copied to the device first, with the clearing (594 workgroups x 64
+    // parents out of pinned memory took it from 22 to 31 us).  The nodes'
+    // items are built and copied while it runs.
+    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), dslots, clear, s);
+    TS_HIP(hipGetLastError());
+    clear = 0;
+    if (nz > 0) {
+      const Plan pl = make_plan(d, nz, T, TS_SAMPLER_GUMBEL, true);
+      launch_eval(d, eval_params(d, reinterpret_cast<const ts_parent*>(ws + vl.off_par), nz, T, seed, pl, nullptr, zbuf),
+                  pl, s);
+      TS_HIP(hipGetLastError());
+    }
+    VerifyNext* hnext = reinterpret_cast<VerifyNext*>(hitem + nn);
+    int mmax = 0;
+    for (int i = 0, z = 0; i < nn; ++i) {
+      const int q = nodes[i] / cap;
+      const size_t row = (size_t)q * cap, o = nodes[i];
       VerifyItem it{};
+      VerifyNext nx{};
       it.request = q;
-      it.node = cur[q];
+      it.node = nodes[i] % cap;
       it.depth = tree->depth[o];
       it.path = tree->path[o];
-      const int* ch = kids.first(q, cur[q]);
-      it.m = std::min(kids.count(q, cur[q]), TS_MAX_K);
-      for (int j = 0; j < it.m; ++j) it.child_tok[j] = tree->token[(size_t)q * cap + ch[j]];
-      it.zrow = -1;
-      if (it.m > 0) {
-        it.zrow = (int)zpar.size();
-        zpar.push_back(ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]});
+      const int* ch = kids.first(q, it.node);
+      it.m = std::min(kids.count(q, it.node), TS_MAX_K);
+      for (int j = 0; j < it.m; ++j) {
+        it.child_tok[j] = tree->token[row + ch[j]];
+        nx.child_node[j] = ch[j];
+        nx.child_path[j] = tree->path[row + ch[j]];
+        nx.child_item[j] = kids.count(q, ch[j]) == 0 ? kNextLeaf : node_at[row + ch[j]];
       }
-      items.push_back(it);
+      it.zrow = it.m > 0 ? z++ : -1;
+      mmax = std::max(mmax, it.m);
+      hitem[i] = it;
+      hnext[i] = nx;
     }
-    const int ni = (int)items.size();
-    if (first_level) {
-      if ((int)zpar.size() != first_rows)
-        return fail(TS_EINTERNAL, "first verification level has %d recompute rows, %d queued", (int)zpar.size(),
-                    first_rows);
-    } else if (!zpar.empty()) {
-      // the recompute reads its parents from the pinned buffer
-      std::memcpy(hs + hs_items, zpar.data(), zpar.size() * sizeof(ts_parent));
-      if ((rc = launch_recompute((int)zpar.size())) != TS_OK) return rc;
-    }
-    first_level = false;
-    // pass A reads the items from the pinned buffer and stages them in ditems
-    std::memcpy(hs, items.data(), ni * sizeof(VerifyItem));
+    for (int o : nodes) node_at[o] = kNextHost;
+    VerifyItem* ditems = reinterpret_cast<VerifyItem*>(ws + vl.off_items);
+    VerifyNext* dnext = reinterpret_cast<VerifyNext*>(ditems + nn);
+    static_assert(sizeof(VerifyItem) % 8 == 0 && sizeof(VerifyNext) % 8 == 0, "aligned one after the other");
+    launch_verify_stage_in(hitem, ditems, nn * (sizeof(VerifyItem) + sizeof(VerifyNext)), nullptr, 0, s);
+    TS_HIP(hipGetLastError());
     VerifyPass vp{};
     vp.target = target;
     vp.cap = cap;
     vp.V = V;
     vp.items = ditems;
-    vp.items_host = reinterpret_cast<const VerifyItem*>(hs);
-    vp.items_w = ditems;
     vp.nitems = ni;
     vp.zbuf = zbuf;
     vp.c = kLog2e / T;
@@ -1321,15 +1397,11 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     vp.bp = reinterpret_cast<VBonusPart*>(ws + vl.off_bp);
     vp.consts = reinterpret_cast<VConst*>(ws + vl.off_cst);
     vp.recs = reinterpret_cast<VRec*>(ws + vl.off_rec);
-    vp.results = const_cast<VerifyResult*>(res);  // pinned: the resolve kernel writes it
-    int mmax = 0;
-    for (const VerifyItem& it : items) mmax = std::max(mmax, it.m);
-    const FusedPlan fp = thread_state().verify_mode == TS_VERIFY_STAGED ? FusedPlan{false, 0, 0}
-                                                                          : fused_plan(V, ni, bf16);
+    vp.results = res;  // pinned: the resolve kernel writes it
+    bool staged = !fp.ok;
     if (fp.ok) {
-      ++thread_state().fused_levels;
-      // one launch for the level; a wait that ran out (some workgroup was
-      // not resident) sends the level through the per-stage launches
+      // one launch for the round; a wait that ran out (some workgroup was
+      // not resident) sends its first level through the per-stage launches
       VerifyPass fvp = vp;
       fvp.nchunks = fp.cpi;
       fvp.chunk = fp.chunk;
@@ -1337,58 +1409,70 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       f.cpi = fp.cpi;
       f.chunk = fp.chunk;
       f.slots = dslots;
-      f.epoch = ++epoch;
+      f.epoch = epoch;
       f.err = derr;
       f.herr = const_cast<int32_t*>(herr);
       f.spin_limit = kFusedSpinLimit;
-      f.next_host = hnext;
-      // each item's children: node, path, and whether the walk ends there
-      for (int i = 0; i < ni; ++i) {
-        const VerifyItem& it = items[i];
-        VerifyNext nx{};
-        const int* ch = kids.first(it.request, it.node);
-        for (int j = 0; j < it.m; ++j) {
-          const size_t o = (size_t)it.request * cap + ch[j];
-          nx.child_node[j] = ch[j];
-          nx.child_path[j] = tree->path[o];
-          if (kids.count(it.request, ch[j]) == 0) nx.leaf_mask |= 1u << j;
-        }
-        hnext[i] = nx;
-      }
+      f.next = dnext;
+      f.done = done;
+      std::fill(done, done + (size_t)ni * kDoneWords, 0ull);
       *herr = 0;
       launch_verify_fused(fvp, f, bf16, s);
       TS_HIP(hipGetLastError());
-      TS_HIP(hipStreamSynchronize(s));
-      if (*herr != 0) {
+      bool failed = false;
+      if ((rc = wait_round(done, ni * kDoneWords, epoch, herr, s, &failed)) != TS_OK) return rc;
+      epoch += TS_MAX_D + 1;  // a walk's levels, and the leaf it ends at
+      if (failed) {
+        ++thread_state().fused_levels;
         ++thread_state().fused_fallbacks;
-        launch_verify_clear(derr, 1, s);
-        launch_verify_level(vp, bf16, mmax, s);
-        TS_HIP(hipGetLastError());
-        TS_HIP(hipStreamSynchronize(s));
+        launch_verify_stage_in(nullptr, nullptr, 0, derr, 4, s);
+        staged = true;
       }
     } else {
       ++thread_state().staged_levels;
+    }
+    if (staged) {
       launch_verify_level(vp, bf16, mmax, s);
       TS_HIP(hipGetLastError());
       TS_HIP(hipStreamSynchronize(s));
     }
-    std::vector<int> next;
+    next.clear();
+    int levels = 0;
     for (int i = 0; i < ni; ++i) {
-      const int q = items[i].request;
-      if (res[i].accepted > 0 && path_len[q] < TS_MAX_D) {
-        const int c = kids.first(q, cur[q])[res[i].accepted - 1];
+      const int q = active[i];
+      int accepted, b;
+      uint64_t digits = 0;
+      bool ended;
+      if (staged) {
+        accepted = res[i].accepted > 0 ? 1 : 0;
+        digits = (uint64_t)(accepted ? res[i].accepted - 1 : 0);
+        b = res[i].bonus;
+        ended = !accepted;
+      } else {
+        const uint64_t* w = done + (size_t)i * kDoneWords;
+        const uint32_t state = (uint32_t)w[kDoneState];
+        accepted = (int)(state & 255u);
+        ended = (state & kDoneEnded) != 0;
+        digits = (uint64_t)(uint32_t)w[kDonePath] | ((uint64_t)(uint32_t)w[kDonePath + 1] << 32);
+        b = (int32_t)(uint32_t)w[kDoneBonus];
+        levels = std::max(levels, std::max(accepted, 1));
+      }
+      for (int l = 0; l < accepted; ++l) {
+        if (path_len[q] >= TS_MAX_D) {
+          ended = true;
+          break;
+        }
+        const int c = kids.first(q, cur[q])[(digits >> (4 * l)) & 15];
         path_nodes[(size_t)q * TS_MAX_D + path_len[q]++] = c;
         cur[q] = c;
-        if (res[i].leaf_bonus)
-          bonus[q] = res[i].bonus;  // the accepted child has no children: its bonus is drawn
-        else
-          next.push_back(q);
-      } else {
-        bonus[q] = res[i].bonus;
       }
+      bonus[q] = b;
+      if (!ended) next.push_back(q);
     }
+    if (!staged) thread_state().fused_levels += levels;
     active.swap(next);
   }
+  TS_HIP(hipStreamSynchronize(s));
   drain.armed = false;
   return TS_OK;
 }

@@ -65,20 +65,25 @@ int verify_fused_blocks_per_cu(bool bf16) {
 void launch_verify_fused(const VerifyPass& vp, const VFused& f, bool bf16, hipStream_t s) {
   const dim3 grid(vp.nitems * f.cpi), block(kVerifyThreads);
   if (bf16)
-    hipLaunchKernelGGL((verify_fused_kernel<uint16_t, kFusedQuadsBf16>), grid, block, 0, s, vp, f);
+    hipLaunchKernelGGL((verify_fused_kernel<uint16_t, kFusedQuadsBf16>), grid, block, 0, s, VFusedArgs{vp, f});
   else
-    hipLaunchKernelGGL((verify_fused_kernel<float, kFusedQuadsF32>), grid, block, 0, s, vp, f);
+    hipLaunchKernelGGL((verify_fused_kernel<float, kFusedQuadsF32>), grid, block, 0, s, VFusedArgs{vp, f});
 }
 
-// Clears n words (the counters and the flag before a ts_verify call's first
-// fused launch).
-__global__ void verify_clear_kernel(int* p, int n) {
+// Copies n16 16-byte pieces (the first level's rows, from the host's pinned
+// buffer) and clears nclear of them (the level slots).
+__global__ void verify_stage_in_kernel(const u32x4* src, u32x4* dst, int n16, u32x4* clear, int nclear) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+  if (i < n16) dst[i] = src[i];
+  if (i < nclear) clear[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
-void launch_verify_clear(int* p, int n, hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(verify_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
+void launch_verify_stage_in(const void* src, void* dst, size_t bytes, void* clear, size_t clear_bytes, hipStream_t s) {
+  const int n16 = (int)((bytes + 15) / 16), nc = (int)((clear_bytes + 15) / 16);
+  const int n = std::max(n16, nc);
+  if (n > 0)
+    hipLaunchKernelGGL(verify_stage_in_kernel, dim3((n + 255) / 256), dim3(256), 0, s, static_cast<const u32x4*>(src),
+                       static_cast<u32x4*>(dst), n16, static_cast<u32x4*>(clear), nc);
 }
 
 }  // namespace ts

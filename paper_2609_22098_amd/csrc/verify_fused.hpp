@@ -1,4 +1,4 @@
-// One launch per level of the T > 0 walk (§3.3, Proposition 1) with the
+// One launch for the levels of the T > 0 walk (§3.3, Proposition 1) with the
 // rows held in registers.
 //
 // The per-stage launches read an item's target and draft rows once for pass A
@@ -15,8 +15,19 @@
 // workgroup that needs the step's total polls the item's slots of that step
 // with agent-scope loads until every chunk's words carry the epoch, and reduces
 // them in the same fixed order, so all workgroups take the same decisions.
-// The slots are cleared once per ts_verify call and each launch of the call
-// has its own epoch, so no stale word matches.  The host sizes the grid to
+// The slots are cleared once per ts_verify call and each level of each launch of
+// the call has its own epoch, so no stale word matches.
+//
+// An accepted child whose logits were recomputed for the same launch is the
+// item's next node: its workgroups go on there without the host.  Items walk
+// independently, and a level taken this way costs the loads and pass A
+// (about 10 us) instead of a recompute, a launch and the host's turn around
+// (about 35 us): 64 requests with trees of up to 8 nodes (V = 151936, bf16, T
+// = 0.7) went from 169 to 131 us, one request with 64 nodes from 126 to 81.  Consecutive levels use the two halves of the item's slots in
+// turn: a workgroup can be one level ahead of another (which still reads the
+// level's words), never two.
+//
+// The host sizes the grid to
 // what the device holds at once, so every workgroup is resident and every wait
 // ends; each wait is also bounded, and one that runs out sets a flag (device
 // and pinned host copies) that ends the other waits early: the host then runs
@@ -36,9 +47,8 @@ constexpr int kFusedQuadsF32 = 6;
 constexpr int kFusedMaxChunks = 32;
 
 // Words of an item's slots, each [cpi] long: pass A (maxima and sums of
-// both rows), the Z_j partial of each stage, the bonus keys' best, second
-// best and token.
-constexpr int kSlotPA = 0, kSlotZ = 4, kSlotB = 4 + TS_MAX_K, kSlotWords = 7 + TS_MAX_K;
+// both rows), the Z_j partial of each stage, the best bonus key and its token.
+constexpr int kSlotPA = 0, kSlotZ = 4, kSlotB = 4 + TS_MAX_K, kSlotWords = 6 + TS_MAX_K;
 // Most chunks of an item in one launch (one polling lane per chunk), and
 // most workgroups of one launch (the slots are sized for that many).
 constexpr int kFusedMaxCpi = 64;
@@ -47,13 +57,41 @@ constexpr int kFusedMaxGrid = 4096;
 struct VFused {
   int cpi;           // chunks per item (<= kFusedMaxCpi)
   int chunk;         // tokens per chunk, a multiple of 4
-  uint64_t* slots;   // [nitems][kSlotWords][cpi]: value bits | epoch << 32
-  uint32_t epoch;    // this launch's tag (slots start the call at zero)
+  uint64_t* slots;   // [2][nitems][kSlotWords][cpi]: value bits | epoch << 32 (one half when no node goes on)
+  uint32_t epoch;    // the first level's tag, the next levels count on (slots start the call at zero)
   int* err;          // device flag: a wait ran out
   int32_t* herr;     // the flag's pinned host copy
   int spin_limit;    // polls before a wait gives up
-  const VerifyNext* next_host;  // [nitems], pinned host memory
+  const VerifyNext* next;  // of the launch's nodes, as vp.items
+  uint64_t* done;    // [nitems][kDoneWords], pinned host memory: the items' results, zero before the launch
 };
+
+// The kernel's only argument.
+struct VFusedArgs {
+  VerifyPass vp;
+  VFused f;
+};
+typedef const __attribute__((address_space(4))) VFusedArgs* FusedArgPtr;
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_assume(!__builtin_amdgcn_is_shared((const void*)p) && !__builtin_amdgcn_is_private((const void*)p));
+#endif
+  return p;
+}
+
+// An item's result: 32-bit words, each stored with the launch's epoch above
+// it (one 64-bit store), so that the host can go on as soon as it has seen
+// every item's words instead of waiting for the launch to end and the stream
+// to report it.
+enum : int {
+  kDoneBonus = 0,   // the bonus token
+  kDonePath = 1,    // and 2: the accepted children's places in draw order, 4 bits a level
+  kDoneState = 3,   // accepted children | kDoneEnded
+  kDoneWords = 4
+};
+constexpr uint32_t kDoneEnded = 256;  // the walk has ended (the bonus counts)
+static_assert(TS_MAX_K <= 16 && TS_MAX_D <= 16, "a level takes 4 bits of two words");
 
 // Quad of target values as loaded: four bf16 in two words, or four floats.
 template <typename TT>
@@ -177,43 +215,32 @@ __device__ __forceinline__ bool poll_slots(const VFused& f, int it, int w0, uint
   }
 }
 
-// Bonus keys of a node without children over the thread's quads of its
-// target row (r = 2^(t c - const): the draw comes from the target itself),
-// reduced over the workgroup; thread 0 stores the chunk's best, second best
-// and token in the bonus slots.
-template <typename Q, int NQ>
-__device__ __forceinline__ void leaf_keys(const Q (&tq)[NQ], int b0, int y1, float c, uint64_t path, uint32_t c3,
-                                          const VerifyPass& vp, const VFused& f, int it, int ck, float* redv,
-                                          int* redi) {
-  const uint32_t pc1 = (uint32_t)path, pc2 = (uint32_t)(path >> 32);
-  BonusTop bt;
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    if (b0 + 1024 * q >= y1) break;
-    // one quad's Philox words at a time: tied to the keys taken so far, the
-    // next quad's words are not computed ahead (register pressure)
-    int bq = b0 + 1024 * q;
-    asm volatile("" : "+v"(bq) : "v"(bt.best));
-    uint32_t w[4];
-    bonus_words(w, bq, pc1, pc2, c3, vp.keys);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bt.add(tquad_at(tq[q], e) * c + gumbel_neg(w[e]), b0 + 1024 * q + e);
+// Best bonus key and its token (smallest on ties).
+struct BonusBest {
+  float best = kNegInf;
+  int idx = 0x7FFFFFFF;
+  __device__ __forceinline__ void add(float key, int y) {
+    if (key > best) { best = key; idx = y; }
   }
+};
+// The workgroup's best key into the chunk's bonus words.
+__device__ __forceinline__ void put_bonus(const BonusBest& bt, const VFused& f, int it, int ck, float* redv, int* redi) {
   float vb = bt.best;
   int id = bt.idx;
   block_argmax(vb, id, redv, redi);
-  float s2 = (bt.idx == id) ? bt.second : bt.best;
-  s2 = block_max(s2, redv);
   if (threadIdx.x == 0) {
     put_slot(f, it, ck, kSlotB, __float_as_uint(vb));
-    put_slot(f, it, ck, kSlotB + 1, __float_as_uint(s2));
-    put_slot(f, it, ck, kSlotB + 2, (uint32_t)id);
+    put_slot(f, it, ck, kSlotB + 1, (uint32_t)id);
   }
 }
 
+// One level of the workgroup's walk; true if the walk goes on to another.  A
+// function of its own: as the body of a loop over the levels, the compiler
+// carried addresses, bounds and masks over the levels and spilled 79 to 151
+// registers in the middle of the work (64 requests, T = 0.7: 178 us); the
+// call saves 48 at its entry instead (157 us).
 template <typename TT, int NQ>
-__global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(4))) void verify_fused_kernel(
-    VerifyPass vp, VFused f) {
+__device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int levelv) {
   using Q = typename TQuad<TT>::type;
   static_assert(4 * NQ <= 64, "a thread's tokens fit the 64-bit child mask");
   __shared__ Q tl[NQ * kVerifyThreads];  // each thread's target quads, [q][thread]
@@ -227,19 +254,59 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
   __shared__ int loc[TS_MAX_K];   // children inside the chunk: token
   __shared__ int locj[TS_MAX_K];  // and its place in the draw order (1-based)
   __shared__ int sh_n, sh_ok;
-  const int it = blockIdx.x / f.cpi, ck = blockIdx.x % f.cpi;
-  if (it >= vp.nitems) return;  // never: the grid is nitems * cpi
+  // the walk: the node it stands at (an index into vp.items), the children
+  // accepted so far (4 bits a level), its level in this launch
+  __shared__ int sh_node;
+  __shared__ uint64_t sh_digits;
   const int tid = threadIdx.x;
   constexpr int kItemWords = (int)(sizeof(VerifyItem) / 4);
   constexpr int kNextWords = (int)(sizeof(VerifyNext) / 4);
   static_assert(kItemWords + kNextWords <= kVerifyThreads, "item and next words");
-  if (tid < kItemWords)
-    reinterpret_cast<int32_t*>(&sitem)[tid] = reinterpret_cast<const int32_t*>(vp.items_host + it)[tid];
+  // function arguments arrive in vector registers
+  const int level = __builtin_amdgcn_readfirstlane(levelv);
+  const uint64_t apb = (uint64_t)apv;
+  const FusedArgPtr ap = (FusedArgPtr)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(apb >> 32)) << 32) |
+                                       (uint32_t)__builtin_amdgcn_readfirstlane((int)apb));
+  // read through the constant address space: scalar loads
+  uint32_t aw[sizeof(VFusedArgs) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(VFusedArgs) / 4; ++i)
+    aw[i] = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(ap)[i];
+  VFusedArgs A;
+  __builtin_memcpy(&A, aw, sizeof(A));
+  // all of them point to global memory (else: flat loads)
+  A.vp.target = as_global(ap->vp.target);
+  A.vp.items = as_global(ap->vp.items);
+  A.vp.zbuf = as_global(ap->vp.zbuf);
+  A.f.slots = as_global(ap->f.slots);
+  A.f.err = as_global(ap->f.err);
+  A.f.herr = as_global(ap->f.herr);
+  A.f.next = as_global(ap->f.next);
+  A.f.done = as_global(ap->f.done);
+  const VerifyPass& vp = A.vp;
+  VFused& f = A.f;
+  const uint32_t epoch0 = f.epoch;
+  const int it = __builtin_amdgcn_readfirstlane((int)blockIdx.x / f.cpi);
+  const int ck = __builtin_amdgcn_readfirstlane((int)blockIdx.x % f.cpi);
+  if (it >= vp.nitems) return false;  // never: the grid is nitems * cpi
+  if (level == 0 && tid == 0) {
+    sh_node = it;
+    sh_digits = 0;
+  }
+  f.epoch += (uint32_t)level;
+  __syncthreads();  // the walk's place is set, the previous level's readers of the shared records are done
+  const int at_node = __builtin_amdgcn_readfirstlane(sh_node);
+  if (at_node < 0)  // an accepted leaf: its item is in place
+    ;
+  else if (tid < kItemWords)
+    reinterpret_cast<int32_t*>(&sitem)[tid] = reinterpret_cast<const int32_t*>(vp.items + at_node)[tid];
   else if (tid < kItemWords + kNextWords)
     reinterpret_cast<int32_t*>(&snext)[tid - kItemWords] =
-        reinterpret_cast<const int32_t*>(f.next_host + it)[tid - kItemWords];
+        reinterpret_cast<const int32_t*>(f.next + at_node)[tid - kItemWords];
   __syncthreads();
-  const int m = sitem.m;
+  const int m = __builtin_amdgcn_readfirstlane(sitem.m);
+  // a leaf uses the bonus words only, which its walk has not used before
+  if (m > 0) f.slots += (size_t)(level & 1) * vp.nitems * kSlotWords * f.cpi;
   const int y0 = ck * f.chunk, y1 = min(vp.V, y0 + f.chunk);
   const TT* trow = static_cast<const TT*>(vp.target) + ((size_t)sitem.request * vp.cap + sitem.node) * vp.V;
   const float* zrow = m > 0 ? vp.zbuf + (size_t)sitem.zrow * vp.V : nullptr;
@@ -256,7 +323,8 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
     sh_n = k;
   }
   // thread t holds the quads y0 + 4 t + 1024 q, q < NQ
-  const int b0 = y0 + 4 * tid;
+  int b0 = y0 + 4 * tid;
+  asm volatile("" : "+v"(b0));
   Q tq[NQ];
   f32x4 zq[NQ];
   if (vector_rows<TT>(vp)) {
@@ -267,7 +335,7 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
     for (int q = 0; q < NQ; ++q) load_quad_tok<TT>(trow, zrow, b0 + 1024 * q, y1, tq[q], zq[q]);
   }
   __syncthreads();
-  const int nloc = sh_n;
+  const int nloc = __builtin_amdgcn_readfirstlane(sh_n);
   const float c = vp.c;
   const uint32_t pc1 = (uint32_t)sitem.path, pc2 = (uint32_t)(sitem.path >> 32);
   const uint32_t c3 = counter_word3(sitem.request, sitem.depth, 3u);
@@ -281,7 +349,22 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
 
   if (m == 0) {
     // leaf: bonus keys from the target row
-    leaf_keys(tq, b0, y1, c, sitem.path, c3, vp, f, it, ck, redv, redi);
+    // (r = 2^(t c - const): the draw comes from the target itself), one quad
+    // of the thread at a time out of LDS
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) tl[q * kVerifyThreads + tid] = tq[q];
+    BonusBest bt;
+#pragma unroll 1
+    for (int q = 0; q < NQ; ++q) {
+      const int bq = b0 + 1024 * q;
+      if (bq >= y1) break;
+      const Q t = tl[q * kVerifyThreads + tid];
+      uint32_t w[4];
+      bonus_words(w, bq, pc1, pc2, c3, vp.keys);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bt.add(tquad_at(t, e) * c + gumbel_neg(w[e]), bq + e);
+    }
+    put_bonus(bt, f, it, ck, redv, redi);
     bonus = true;
   } else {
     // an item with children holds the level's longest chain of steps: its
@@ -368,7 +451,7 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
       if (lane == 0) sh_ok = ok ? 1 : 0;
     }
     __syncthreads();
-    alive = sh_ok != 0;
+    alive = __builtin_amdgcn_readfirstlane(sh_ok) != 0;
     if (alive) {
       rec = shr;
       const float Lt = sC.Lt, Lz = sC.Lz;
@@ -380,7 +463,7 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
         for (int e = 0; e < 4; ++e) zq[q][e] = exp2_fast(zq[q][e] * c - Lz);
       // stage j rejected: Z_j over the tokens not drawn up to j; at the last
       // child the same residual also gives the bonus keys
-      for (int j = 1; rec.status == kRejected; ++j) {
+      for (int j = 1; __builtin_amdgcn_readfirstlane(rec.status) == kRejected; ++j) {
         if (nloc) {
           for (int k = 0; k < nloc; ++k) {
             if (locj[k] != j) continue;
@@ -405,7 +488,7 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
         }
         const float a = rec.alpha, bb = rec.betap;
         if (j == m) {
-          BonusTop bt;
+          BonusBest bt;
 #pragma unroll
           for (int q = 0; q < NQ; ++q) {
             if (b0 + 1024 * q >= y1) break;
@@ -420,16 +503,7 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
               if (r > 0.0f) bt.add(__builtin_amdgcn_logf(r) + gumbel_neg(w[e]), b0 + 1024 * q + e);
             }
           }
-          float vb = bt.best;
-          int id = bt.idx;
-          block_argmax(vb, id, redv, redi);
-          float s2 = (bt.idx == id) ? bt.second : bt.best;
-          s2 = block_max(s2, redv);
-          if (tid == 0) {
-            put_slot(f, it, ck, kSlotB, __float_as_uint(vb));
-            put_slot(f, it, ck, kSlotB + 1, __float_as_uint(s2));
-            put_slot(f, it, ck, kSlotB + 2, (uint32_t)id);
-          }
+          put_bonus(bt, f, it, ck, redv, redi);
           rec.status = kExhausted;
           rec.stage = j + 1;
           bonus = true;
@@ -456,55 +530,67 @@ __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(
           if (tid == 0) sh_ok = ok ? 1 : 0;
         }
         __syncthreads();
-        alive = sh_ok != 0;
+        alive = __builtin_amdgcn_readfirstlane(sh_ok) != 0;
         if (!alive) break;
         rec = shr;
       }
     }
   }
-  // an accepted child without children ends the walk there: its bonus comes
-  // from its own target row, drawn here instead of at the next level
-  bool leaf_next = false;
-  if (alive && m > 0 && rec.status == kAccepted && ((snext.leaf_mask >> (rec.stage - 1)) & 1u)) {
-    leaf_next = true;
-    const int cn = snext.child_node[rec.stage - 1];
-    const TT* crow = static_cast<const TT*>(vp.target) + ((size_t)sitem.request * vp.cap + cn) * vp.V;
-    Q cq[NQ];
-    f32x4 unused[NQ];
-    if (vector_rows<TT>(vp)) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) load_quad_vec<TT>(crow, nullptr, b0 + 1024 * q, y1, cq[q], unused[q]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) load_quad_tok<TT>(crow, nullptr, b0 + 1024 * q, y1, cq[q], unused[q]);
+  const bool ended = bonus;
+  const bool took = alive && m > 0 && __builtin_amdgcn_readfirstlane(rec.status) == kAccepted;
+  if (took) {
+    const int s = __builtin_amdgcn_readfirstlane(rec.stage) - 1;
+    const int ci = __builtin_amdgcn_readfirstlane(snext.child_item[s]);
+    if (tid == 0) {
+      sh_digits |= (uint64_t)s << (4 * level);
+      sh_node = ci;  // >= 0, or set below
     }
-    leaf_keys(cq, b0, y1, c, snext.child_path[rec.stage - 1], counter_word3(sitem.request, sitem.depth + 1, 3u),
-              vp, f, it, ck, redv, redi);
-    bonus = true;
-  }
-  // chunk 0 writes the item's result: the accepted child, or the bonus token
-  // from the chunks' best keys, or both
-  if (ck == 0 && alive && tid < 64) {
-    uint32_t w[3] = {0u, 0u, 0u};
-    const bool ok = bonus ? poll_slots<3>(f, it, kSlotB, w) : true;
-    if (ok) {
-      VRec rr = rec;
-      if (leaf_next) rr.status = kExhausted;  // the bonus part of the result
-      VerifyResult r = verify_result(rr, f.cpi, [&](int) {
-        VBonusPart b;
-        b.best = __uint_as_float(w[0]);
-        b.second = __uint_as_float(w[1]);
-        b.idx = (int32_t)w[2];
-        b.pad = 0;
-        return b;
-      });
-      if (leaf_next) {
-        r.accepted = rec.stage;
-        r.leaf_bonus = 1;
+    // the accepted child's logits are there: the walk goes on at it (a walk
+    // has at most TS_MAX_D levels; the path's digits have room for no more)
+    if (ci >= 0 && level + 1 < TS_MAX_D) return true;
+    if (ci == kNextLeaf) {
+      // a child without children: the next level draws the bonus from its target row
+      if (tid == 0) {
+        sitem.m = 0;
+        sitem.node = snext.child_node[s];
+        sitem.path = snext.child_path[s];
+        sitem.depth += 1;
+        sh_node = -1;
       }
-      // pinned host memory, read by the host after it synchronises the stream
-      if (tid == 0) vp.results[it] = r;
+      return true;
     }
+  }
+  // chunk 0 hands the item's walk to the host: the accepted children, and the
+  // bonus token from the chunks' best keys if it has ended
+  if (ck == 0 && alive && tid < 64) {
+    uint32_t w[2] = {0u, 0u};
+    const bool ok = ended ? poll_slots<2>(f, it, kSlotB, w) : true;
+    if (ok) {
+      float vb = tid < f.cpi ? __uint_as_float(w[0]) : kNegInf;
+      int id = tid < f.cpi ? (int)w[1] : 0x7FFFFFFF;
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) {
+        const float ov = __shfl_xor(vb, o, 64);
+        const int oi = __shfl_xor(id, o, 64);
+        if (ov > vb || (ov == vb && oi < id)) { vb = ov; id = oi; }
+      }
+      const int accepted = level + (took ? 1 : 0);
+      if (tid < kDoneWords) {
+        const uint32_t v = tid == kDoneBonus ? (uint32_t)id
+                           : tid == kDoneState ? (uint32_t)accepted | (ended ? kDoneEnded : 0u)
+                                               : (uint32_t)(sh_digits >> (32 * (tid - kDonePath)));
+        __hip_atomic_store(f.done + (size_t)it * kDoneWords + tid, ((uint64_t)epoch0 << 32) | v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+    }
+  }
+  return false;
+}
+
+template <typename TT, int NQ>
+__global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(4))) void verify_fused_kernel(
+    const VFusedArgs) {
+  for (int level = 0; fused_level<TT, NQ>((FusedArgPtr)__builtin_amdgcn_kernarg_segment_ptr(), level); ++level) {
   }
 }
 

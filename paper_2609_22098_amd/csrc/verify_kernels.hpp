@@ -45,9 +45,9 @@ typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4 quad_words(const float* p) { return *reinterpret_cast<const f32x4_a4*>(p); }
 __device__ __forceinline__ uint2 quad_words(const uint16_t* p) {
-  const uintptr_t a = reinterpret_cast<uintptr_t>(p);
-  const uint32_t sh = (uint32_t)(a & 2) << 3;
-  const u32x2_a4 d = *reinterpret_cast<const u32x2_a4*>(a & ~(uintptr_t)3);
+  const uint32_t odd = (uint32_t)(reinterpret_cast<uintptr_t>(p) >> 1) & 1u;
+  const uint32_t sh = odd << 4;
+  const u32x2_a4 d = *reinterpret_cast<const u32x2_a4*>(p - odd);
   const uint32_t last = p[3];
   return uint2{__builtin_amdgcn_alignbit(d[1], d[0], sh), __builtin_amdgcn_alignbit(last, d[1], sh)};
 }
@@ -284,19 +284,19 @@ struct VerifyItem {
 
 struct VerifyResult {
   int32_t accepted;  // 1-based sibling index of the accepted child, 0 = none
-  int32_t bonus;     // bonus token when accepted == 0, or at the accepted leaf (leaf_bonus)
+  int32_t bonus;     // bonus token when accepted == 0
   float margin;      // smallest |log u - log ratio| (or bonus key gap)
-  int32_t leaf_bonus;  // 1: the accepted child has no children and bonus is its draw
+  int32_t pad;
 };
 
-// The children of a level item as the one-launch level needs them to carry
-// on into an accepted child without children: its node, its path and whether
-// it has children (pinned host memory, one per item).
+// The children of a node as the one-launch level needs them to carry on into
+// an accepted one: node, path, and where its own VerifyItem is.
+enum : int32_t { kNextLeaf = -1, kNextHost = -2 };
 struct VerifyNext {
   int32_t child_node[TS_MAX_K];
+  int32_t child_item[TS_MAX_K];  // index among the launch's nodes; kNextLeaf: it has no children; kNextHost: it
+                                 // has some, but its logits were not recomputed for this launch
   uint64_t child_path[TS_MAX_K];
-  uint32_t leaf_mask;  // bit s: child s (draw order) has no children
-  int32_t pad;
 };
 
 // ---- T > 0: passes over (item, vocabulary chunk) workgroups ----------------
@@ -333,9 +333,7 @@ struct VRec;
 struct VerifyPass {
   const void* target;  // [R][cap][V]
   int cap, V;
-  const VerifyItem* items;       // [nitems], device copy (staged by pass A)
-  const VerifyItem* items_host;  // [nitems], pinned host memory: read by pass A only
-  VerifyItem* items_w;           // the device copy, written by pass A
+  const VerifyItem* items;  // the items' nodes at [0, nitems); the one-launch level also reads the nodes after them
   int nitems;
   const float* zbuf;   // recomputed draft logits, row items[i].zrow
   float c;             // log2(e) / T
@@ -672,13 +670,8 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_pass_a_kernel(VerifyPas
   static_assert(sizeof(VerifyItem) % 4 == 0 && sizeof(VerifyItem) / 4 <= kVerifyThreads, "item words");
   const int it = blockIdx.x / vp.nchunks, ck = blockIdx.x % vp.nchunks;
   if (it >= vp.nitems) return;
-  // the item from the host's pinned buffer; chunk 0 also stages it for the
-  // level's later kernels
-  if (threadIdx.x < (int)(sizeof(VerifyItem) / 4)) {
-    const int32_t w = reinterpret_cast<const int32_t*>(vp.items_host + it)[threadIdx.x];
-    reinterpret_cast<int32_t*>(&sitem)[threadIdx.x] = w;
-    if (ck == 0) reinterpret_cast<int32_t*>(vp.items_w + it)[threadIdx.x] = w;
-  }
+  if (threadIdx.x < (int)(sizeof(VerifyItem) / 4))
+    reinterpret_cast<int32_t*>(&sitem)[threadIdx.x] = reinterpret_cast<const int32_t*>(vp.items + it)[threadIdx.x];
   __syncthreads();
   const VerifyItem& item = sitem;
   const int y0 = ck * vp.chunk, y1 = min(vp.V, y0 + vp.chunk);
@@ -904,7 +897,7 @@ __device__ VerifyResult verify_result(const VRec& v, int nc, BonusAt&& bp_at) {
   r.accepted = v.status == kAccepted ? v.stage : 0;
   r.bonus = -1;
   r.margin = v.margin;
-  r.leaf_bonus = 0;
+  r.pad = 0;
   if (v.status != kAccepted) {
     float best = kNegInf, second = kNegInf;
     int idx = 0x7FFFFFFF;
