@@ -113,10 +113,12 @@ struct Frag;
 template <>
 struct Frag<uint16_t> {
   typedef bf16x8 type;
-  static constexpr int kPerStep = 32;
-  __device__ static __forceinline__ type load(const uint16_t* row, int k0, int kb) {
-    const uint4 v = *reinterpret_cast<const uint4*>(row + k0 + kb * 8);
-    return __builtin_bit_cast(type, v);
+  // lane group kb's KS operands of a row
+  template <int KS>
+  __device__ static __forceinline__ void load_row(const uint16_t* row, int kb, type (&f)[KS]) {
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+      f[kk] = __builtin_bit_cast(type, *reinterpret_cast<const uint4*>(row + kk * 32 + kb * 8));
   }
   __device__ static __forceinline__ type zero() {
     uint4 v = {0u, 0u, 0u, 0u};
@@ -128,13 +130,24 @@ struct Frag<uint16_t> {
   __device__ static __forceinline__ float to_f32(uint16_t v) { return bf16_to_f32(v); }
 };
 
-// f32: 16x16x4 MFMA; a lane holds one K value of one row/column.
+// f32: 16x16x4 MFMA; a lane holds one K value of one row/column.  Lane group
+// kb takes K = 16 j + 4 kb + i in product 4 j + i: any order of K serves as long
+// as both operands (and every recompute) follow it, and in this one a lane's
+// operands of four products are one 16-byte load.  With K = 4 kk + kb each was
+// a 4-byte load, 64 of them per 64-token step at r = 64 (rows are 16-byte
+// aligned: r is a multiple of 16).
 template <>
 struct Frag<float> {
   typedef float type;
-  static constexpr int kPerStep = 4;
-  __device__ static __forceinline__ type load(const float* row, int k0, int kb) {
-    return row[k0 + kb];
+  template <int KS>
+  __device__ static __forceinline__ void load_row(const float* row, int kb, type (&f)[KS]) {
+    static_assert(KS % 4 == 0, "four products per load");
+#pragma unroll
+    for (int j = 0; j < KS / 4; ++j) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(row + 16 * j + 4 * kb);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[4 * j + i] = v[i];
+    }
   }
   __device__ static __forceinline__ type zero() { return 0.0f; }
   __device__ static __forceinline__ f32x4 mma(type a, type b, f32x4 c) {
@@ -182,8 +195,9 @@ struct URun<uint16_t> {
 template <>
 struct URun<float> {
   float f[16];
+  // rows start at any element: a 16-byte load needs a 4-byte boundary only
   __device__ __forceinline__ void load(const float* row, int t) {
-    const f32x4* p = reinterpret_cast<const f32x4*>(row + t);
+    const f32x4_any* p = reinterpret_cast<const f32x4_any*>(row + t);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const f32x4 v = __builtin_nontemporal_load(p + i);
@@ -395,7 +409,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
   const TE* E = static_cast<const TE*>(p.E);
   const TE* W2 = static_cast<const TE*>(p.W2);
   const int V = p.V, r = p.r;
-  const bool vec_ok = (V % (16 / (int)sizeof(TE))) == 0;
+  const bool vec_ok = sizeof(TE) == 4 || V % 8 == 0;  // 2-byte rows: only at 16-byte boundaries
 
   // Per-column parent state (this lane's parent in each of the NB blocks).
   const TE* urow[NB];
@@ -416,8 +430,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
     }
     urow[nb] = U + ((size_t)req * p.D + dep) * (size_t)V;
     const TE* erow = E + (size_t)tok * r;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) bfrag[nb][kk] = F::load(erow, kk * F::kPerStep, g);
+    F::load_row(erow, g, bfrag[nb]);
     pc1[nb] = (uint32_t)path;
     pc2[nb] = (uint32_t)(path >> 32);
     pc3[nb] = counter_word3(req, dep, 1u);
@@ -445,9 +458,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 #pragma unroll
     for (int bb = 0; bb < 4; ++bb) {
       const int tA = min(t0 + (n >> 2) * 16 + bb * 4 + (n & 3), V - 1);
-      const TE* wrow = W2 + (size_t)tA * r;
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) afrag[bb][kk] = F::load(wrow, kk * F::kPerStep, g);
+      F::load_row(W2 + (size_t)tA * r, g, afrag[bb]);
     }
   };
 
@@ -479,10 +490,10 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
       if constexpr (STORE_Z) {
         if (pidx[nb] < P) {
           float* zo = p.z_out + (size_t)pidx[nb] * V;
-          if ((V & 3) == 0 && tl + 16 <= V) {  // 16-byte aligned: four vector stores
+          if (tl + 16 <= V) {  // four vector stores
 #pragma unroll
             for (int j = 0; j < 16; j += 4)
-              *reinterpret_cast<f32x4*>(zo + tl + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+              *reinterpret_cast<f32x4_any*>(zo + tl + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
           } else {
 #pragma unroll
             for (int j = 0; j < 16; ++j)
@@ -781,8 +792,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     ush[nb] = (uoff[nb] & 2u) << 3;
     if constexpr (RAG) uoff[nb] &= ~3u;
     const uint16_t* erow = E + (size_t)tok * r;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) bfrag[nb][kk] = F::load(erow, kk * F::kPerStep, g);
+    F::load_row(erow, g, bfrag[nb]);
     pc1[nb] = (uint32_t)path;
     pc2[nb] = (uint32_t)(path >> 32);
     pc3[nb] = counter_word3(req, dep, 1u);
@@ -1236,8 +1246,7 @@ __global__ __launch_bounds__(256) void logits_store_kernel(const ExpandParams p)
   }
   FT efrag[KS];
   const uint16_t* erow = static_cast<const uint16_t*>(p.E) + (size_t)tok * r;
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) efrag[kk] = F::load(erow, kk * F::kPerStep, g);
+  F::load_row(erow, g, efrag);
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(efrag[kk]));  // resident before the first queued load
   // byte offsets: of the lane's two U pieces, of its extra word (RAG), of its

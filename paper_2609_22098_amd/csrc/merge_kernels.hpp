@@ -127,8 +127,8 @@ __device__ __forceinline__ void u_seeds(const TE* urow, int tok0, int V, float (
   for (int e = 0; e < 4; ++e) u[e] = tok0 + e < V ? Frag<TE>::to_f32(raw[e]) : kNegInf;
 }
 // The same four seeds with one vector load, for a group that starts at a
-// multiple of 4 inside a row of V % 4 == 0 tokens (the row then starts 8-byte
-// aligned for bf16, 16-byte for f32) and ends at or before V.
+// multiple of 4 and ends at or before V: in bf16 inside a row of V % 4 == 0
+// tokens (the row then starts 8-byte aligned), in f32 inside any row.
 __device__ __forceinline__ void u_seeds4(const uint16_t* p, float (&u)[4]) {
   const uint2 w = *reinterpret_cast<const uint2*>(p);
   u[0] = __uint_as_float(w.x << 16);
@@ -137,11 +137,9 @@ __device__ __forceinline__ void u_seeds4(const uint16_t* p, float (&u)[4]) {
   u[3] = __uint_as_float(w.y & 0xFFFF0000u);
 }
 __device__ __forceinline__ void u_seeds4(const float* p, float (&u)[4]) {
-  const float4 v = *reinterpret_cast<const float4*>(p);
-  u[0] = v.x;
-  u[1] = v.y;
-  u[2] = v.z;
-  u[3] = v.w;
+  const f32x4 v = *reinterpret_cast<const f32x4_any*>(p);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) u[e] = v[e];
 }
 
 // Recompute up to kBatch runs of 16 tokens [t, t+16) for one parent with the
@@ -167,7 +165,7 @@ __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* uro
   f32x4 acc[kBatch];
   const uint32_t col0 = opaque_mask(n == 0);
   // whole aligned runs take vector seed loads (uniform over the wave)
-  bool vec = (V & 3) == 0;
+  bool vec = sizeof(TE) == 4 || (V & 3) == 0;
 #pragma unroll
   for (int b = 0; b < kBatch; ++b) {
     const int tb = b < nrun ? t[b] : 0;
@@ -183,9 +181,7 @@ __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* uro
     for (int i = 0; i < kHalf; ++i) {
       const int b = h * kHalf + i;
       const int tb = b < nrun ? t[b] : 0;
-      const TE* wrow = W2 + (size_t)min(tb + n, V - 1) * p.r;
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) wf[i][kk] = F::load(wrow, kk * F::kPerStep, g);
+      F::load_row(W2 + (size_t)min(tb + n, V - 1) * p.r, g, wf[i]);
     }
     if (vec) {
 #pragma unroll
@@ -642,9 +638,7 @@ __device__ __forceinline__ void seq_draws_n(const MergeParams& p, int pidx, cons
     typename F::type wf[4][KS];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const TE* wrow = W2 + (size_t)min(t0 + 16 * q + n, V - 1) * p.r;
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) wf[q][kk] = F::load(wrow, kk * F::kPerStep, g);
+      F::load_row(W2 + (size_t)min(t0 + 16 * q + n, V - 1) * p.r, g, wf[q]);
     }
     const float useed = keep_or(F::to_f32(urow[min(y, V - 1)]), opaque_mask(y < V), kNegInf);
     // while the block's rows are in flight: the log-mass of the segment's
@@ -780,7 +774,8 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
   const TE* erow = static_cast<const TE*>(p.E) + (size_t)par.token * p.r;
   FT bcol[KS];
 #pragma unroll
-  for (int kk = 0; kk < KS; ++kk) bcol[kk] = (n == 0) ? F::load(erow, kk * F::kPerStep, g) : F::zero();
+  for (int kk = 0; kk < KS; ++kk) bcol[kk] = F::zero();
+  if (n == 0) F::load_row(erow, g, bcol);
   const uint32_t pc1 = (uint32_t)par.path, pc2 = (uint32_t)(par.path >> 32);
   const uint32_t pc3 = counter_word3(par.request, par.depth, 1u);
 
@@ -792,8 +787,7 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
       // the parent's E fragment on every lane: the A operand of the draws'
       // block recompute
       FT eall[KS];
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) eall[kk] = F::load(erow, kk * F::kPerStep, g);
+      F::load_row(erow, g, eall);
       RegList dl;
       reglist_init(dl);
       seq_draws<TE, KS>(p, pidx, urow, eall, pc1, pc2, counter_word3(par.request, par.depth, 4u), sh.d, dl);
