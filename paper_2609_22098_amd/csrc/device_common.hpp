@@ -24,6 +24,11 @@ struct PhiloxKeys {
   uint32_t k1[10];
 };
 
+// a ^ b ^ c as one instruction (the compiler makes two of the operators).
+__device__ __forceinline__ uint32_t xor3_u32(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of the multiply-hi/lo
 // bijection.  Each 32x32 product is one 64-bit multiply.
 __device__ __forceinline__ void philox10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
@@ -32,8 +37,8 @@ __device__ __forceinline__ void philox10(uint32_t& c0, uint32_t& c1, uint32_t& c
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k.k0[r];
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k.k1[r];
+    const uint32_t n0 = xor3_u32((uint32_t)(p1 >> 32), c1, k.k0[r]);
+    const uint32_t n2 = xor3_u32((uint32_t)(p0 >> 32), c3, k.k1[r]);
     c1 = (uint32_t)p1;
     c3 = (uint32_t)p0;
     c0 = n0;
