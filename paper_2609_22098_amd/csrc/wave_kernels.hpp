@@ -24,9 +24,9 @@
 namespace ts {
 
 __device__ __forceinline__ bool wslot_before(const WaveSlot& a, const WaveSlot& b) {
-  if (a.key != b.key) return a.key > b.key;
-  if (a.depth != b.depth) return a.depth < b.depth;
-  return a.path < b.path;
+  // without short-circuit branches
+  const bool deeper = (a.depth < b.depth) | ((a.depth == b.depth) & (a.path < b.path));
+  return (a.key > b.key) | ((a.key == b.key) & deeper);
 }
 
 // Exclusive scan of one int per thread of the workgroup (total: the sum of
@@ -72,51 +72,12 @@ __global__ __launch_bounds__(kWaveThreads) void wave_init_kernel(const WaveParam
   wp.span[0][q] = WaveSpan{q, 1};
 }
 
-// After wave w's expansion: one workgroup per request.  The host guarantees
-// N <= kWaveMaxN and (parents of a request in a wave) x K <= kWaveMaxNew.
-__global__ __launch_bounds__(kWaveThreads) void wave_control_kernel(const WaveParams wp, int w) {
-  __shared__ WaveSlot Ls[kWaveMaxN];
-  __shared__ WaveSlot Ns[kWaveMaxNew];
-  __shared__ int rank_l[kWaveMaxN];
-  __shared__ int rank_n[kWaveMaxNew];
-  __shared__ int order[kWaveMaxNew];  // the new children's indices in pop order
-  __shared__ int tmp[kWaveThreads];
-  __shared__ int base_sh;
-  const int q = blockIdx.x, t = threadIdx.x;
-  const int N = wp.N, K = wp.K;
-  const WaveSpan sp = wp.span[w & 1][q];
-  const ts_parent* par = wp.par[w & 1];
-  const int s = wp.lsize[q];
-  const float lt = wp.log_theta[q];
-  WaveSlot* lq = wp.list + (size_t)q * N;
-  for (int i = t; i < s; i += kWaveThreads) Ls[i] = lq[i];
-
-  // the request's children of this wave with key >= log(theta), in (row, child) order
-  const int mraw = sp.cnt * K;
-  const int per = (mraw + kWaveThreads - 1) / kWaveThreads;
-  const int k0 = min(t * per, mraw), k1 = min(k0 + per, mraw);
-  int c = 0;
-  for (int k = k0; k < k1; ++k) c += wp.slot_key[(size_t)sp.off * K + k] >= lt ? 1 : 0;
-  int m = 0;
-  int pos = wave_block_excl_scan(c, tmp, m);
-  for (int k = k0; k < k1; ++k) {
-    const size_t o = (size_t)sp.off * K + k;
-    const float key = wp.slot_key[o];
-    if (!(key >= lt)) continue;
-    const ts_parent pa = par[sp.off + k / K];
-    const int j = k % K;
-    WaveSlot sl;
-    sl.key = key;
-    sl.depth = pa.depth + 1;
-    sl.path = pa.path | ((uint64_t)j << (4 * pa.depth));
-    sl.token = wp.child_token[o];
-    sl.log_surv = wp.child_log_surv[o];
-    sl.log_q0 = wp.child_log_q0[o];
-    sl.log_qT = wp.child_log_qT[o];
-    Ns[pos++] = sl;
-  }
-  __syncthreads();
-
+// Ranks of the m new slots Ns (any order) and of the s list slots Ls (sorted)
+// in the merged pop order, by a sort.  order: kWaveMaxNew ints of LDS.  The
+// whole workgroup calls it; the ranks are complete after the next barrier.
+__device__ __forceinline__ void rank_by_sort(const WaveSlot* Ns, int m, const WaveSlot* Ls, int s, int* order,
+                                             int* rank_n, int* rank_l) {
+  const int t = threadIdx.x;
   // The new children in pop order: a bitonic sort of their indices over the
   // next power of two (entries past m sort last).  Slots are distinct (their
   // paths differ), so the order is total and the sort's result unique.
@@ -164,6 +125,95 @@ __global__ __launch_bounds__(kWaveThreads) void wave_control_kernel(const WavePa
       if (wslot_before(Ns[order[mid]], a)) lo = mid + 1; else hi = mid;
     }
     rank_l[i] = i + lo;
+  }
+}
+
+// After wave w's expansion: one workgroup per request.  The host guarantees
+// N <= kWaveMaxN and (parents of a request in a wave) x K <= kWaveMaxNew.
+// Bound by latency: one request's trees leave the rest of the chip idle, and
+// each dependent step is a memory round trip or a barrier.  So every load is
+// issued in one of two round trips, children that the full list's last slot
+// already beats are dropped at once (from the third wave on that leaves a
+// few dozen of 64 x 8), and ranks come from counting the slots ahead.
+// kCountLimit: pairs up to which counting is taken; past it the sort's
+// log^2 steps cost less than the pairs / kWaveThreads comparisons of a thread.
+constexpr int kCountLimit = 128 * kWaveThreads;
+__global__ __launch_bounds__(kWaveThreads) void wave_control_kernel(const WaveParams wp, int w) {
+  __shared__ WaveSlot Ls[kWaveMaxN];
+  __shared__ WaveSlot Ns[kWaveMaxNew];
+  __shared__ int rank_l[kWaveMaxN];
+  __shared__ int rank_n[kWaveMaxNew];
+  __shared__ int order[kWaveMaxNew];  // the new children's indices in pop order
+  __shared__ int tmp[kWaveThreads];
+  __shared__ int base_sh;
+  const int q = blockIdx.x, t = threadIdx.x;
+  const int N = wp.N, K = wp.K;
+  const WaveSpan sp = wp.span[w & 1][q];
+  const ts_parent* par = wp.par[w & 1];
+  const int s = wp.lsize[q];
+  const float lt = wp.log_theta[q];
+  WaveSlot* lq = wp.list + (size_t)q * N;
+  const float last = lq[N - 1].key;  // the N-th known slot's, once the list is full
+  // a child below the N-th of a full list ranks past N: neither a slot nor a parent
+  const float cut = s == N ? fmaxf(lt, last) : lt;
+  for (int i = t; i < s; i += kWaveThreads) Ls[i] = lq[i];
+
+  // the request's children of this wave with key >= cut, thread by thread
+  constexpr int kMine = kWaveMaxNew / kWaveThreads;
+  const int mraw = sp.cnt * K;
+  WaveSlot sl[kMine];
+  uint32_t keep = 0u;
+#pragma unroll
+  for (int i = 0; i < kMine; ++i) {
+    const int k = t + i * kWaveThreads;
+    if (i * kWaveThreads < mraw) {  // uniform
+      const int kc = min(k, mraw - 1);
+      const size_t o = (size_t)sp.off * K + kc;
+      const ts_parent pa = par[sp.off + kc / K];
+      sl[i].key = wp.slot_key[o];
+      sl[i].depth = pa.depth + 1;
+      sl[i].path = pa.path | ((uint64_t)(kc % K) << (4 * pa.depth));
+      sl[i].token = wp.child_token[o];
+      sl[i].log_surv = wp.child_log_surv[o];
+      sl[i].log_q0 = wp.child_log_q0[o];
+      sl[i].log_qT = wp.child_log_qT[o];
+      keep |= (k < mraw) & (sl[i].key >= cut) ? 1u << i : 0u;
+    }
+  }
+  int m = 0;
+  int pos = wave_block_excl_scan(__popc(keep), tmp, m);
+#pragma unroll
+  for (int i = 0; i < kMine; ++i)
+    if ((keep >> i) & 1u) {
+      rank_n[pos] = 0;
+      Ns[pos++] = sl[i];
+    }
+  for (int i = t; i < s; i += kWaveThreads) rank_l[i] = i;
+  __syncthreads();
+
+  if (m * (m + 2 * s) <= kCountLimit) {
+    // rank of x in the merged pop order: the slots ahead of it, counted by
+    // several threads per slot, each over its share of the others
+    auto shares = [](int n) {  // threads per slot: kWaveThreads / (n rounded up to a power of two)
+      return n <= 1 ? kWaveThreads : n > kWaveThreads / 2 ? 1 : kWaveThreads >> (32 - __clz(n - 1));
+    };
+    const int gn = shares(m), sn = kWaveThreads / gn;
+    for (int k = t & (sn - 1); k < m; k += sn) {
+      const WaveSlot a = Ns[k];
+      int ahead = 0;
+      for (int i = t / sn; i < m; i += gn) ahead += wslot_before(Ns[i], a) ? 1 : 0;
+      for (int i = t / sn; i < s; i += gn) ahead += wslot_before(Ls[i], a) ? 1 : 0;
+      if (ahead) atomicAdd(&rank_n[k], ahead);
+    }
+    const int gl = shares(s), sl2 = kWaveThreads / gl;
+    for (int k = t & (sl2 - 1); k < s; k += sl2) {
+      const WaveSlot a = Ls[k];
+      int ahead = 0;
+      for (int i = t / sl2; i < m; i += gl) ahead += wslot_before(Ns[i], a) ? 1 : 0;
+      if (ahead) atomicAdd(&rank_l[k], ahead);
+    }
+  } else {
+    rank_by_sort(Ns, m, Ls, s, order, rank_n, rank_l);
   }
   __syncthreads();
   const int total = s + m;
