@@ -3,5 +3,5 @@
 #include "expand_inst.hpp"
 
 namespace ts {
-template void launch_merge_t<uint16_t, 4>(const MergeParams&, int, dim3, dim3, hipStream_t);
+template void launch_merge_t<uint16_t, 4>(const MergeParams&, int, bool, dim3, dim3, hipStream_t);
 }  // namespace ts

@@ -3,6 +3,6 @@
 
 namespace ts {
 template void launch_eval_t<float, 8>(const ExpandParams&, int, int, bool, EvalPath, dim3, dim3, hipStream_t);
-template void launch_merge_t<float, 8>(const MergeParams&, int, dim3, dim3, hipStream_t);
+template void launch_merge_t<float, 8>(const MergeParams&, int, bool, dim3, dim3, hipStream_t);
 template int eval_blocks_per_cu_t<float, 8>(int, int, bool, EvalPath, int);
 }  // namespace ts

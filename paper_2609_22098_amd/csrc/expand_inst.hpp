@@ -72,13 +72,14 @@ int eval_blocks_per_cu_t(int nb, int mode, bool store_z, EvalPath path, int bloc
 }
 
 template <typename TE, int KS>
-void launch_merge_t(const MergeParams& p, int mode, dim3 grid, dim3 block, hipStream_t s) {
+void launch_merge_t(const MergeParams& p, int mode, bool coop, dim3 grid, dim3 block, hipStream_t s) {
+  void (*kernel)(MergeParams) =
+      coop ? expand_merge_kernel<TE, KS, kModeGreedy, true> : expand_merge_kernel<TE, KS, kModeGreedy, false>;
   if (mode == kModeGumbel)
-    hipLaunchKernelGGL((expand_merge_kernel<TE, KS, kModeGumbel>), grid, block, 0, s, p);
-  else if (mode == kModeSeq)
-    hipLaunchKernelGGL((expand_merge_kernel<TE, KS, kModeSeq>), grid, block, 0, s, p);
-  else
-    hipLaunchKernelGGL((expand_merge_kernel<TE, KS, kModeGreedy>), grid, block, 0, s, p);
+    kernel = coop ? expand_merge_kernel<TE, KS, kModeGumbel, true> : expand_merge_kernel<TE, KS, kModeGumbel, false>;
+  if (mode == kModeSeq)
+    kernel = expand_merge_kernel<TE, KS, kModeSeq, false>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, s, p);
 }
 
 }  // namespace ts

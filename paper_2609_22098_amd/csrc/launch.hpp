@@ -20,9 +20,10 @@ void launch_eval_t(const ExpandParams& p, int nb, int mode, bool store_z, EvalPa
 // Resident blocks per CU of the streaming kernel a launch would use (0 if unknown).
 template <typename TE, int KS>
 int eval_blocks_per_cu_t(int nb, int mode, bool store_z, EvalPath path, int block);
-// Per-parent merge: exact top-k, the draws, child scoring.
+// Per-parent merge: exact top-k, the draws, child scoring.  coop: the kernel
+// with workgroups of kCoopWaves waves.
 template <typename TE, int KS>
-void launch_merge_t(const MergeParams& p, int mode, dim3 grid, dim3 block, hipStream_t s);
+void launch_merge_t(const MergeParams& p, int mode, bool coop, dim3 grid, dim3 block, hipStream_t s);
 
 // Verification.
 // Pieces a row is cut into for the argmax of nrows rows (at most `most`), and

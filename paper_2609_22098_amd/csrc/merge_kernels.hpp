@@ -46,7 +46,6 @@ struct MergeLds {
   int item_t[kItemCap];  // run start token, or -(chunk+1) for a whole chunk
   int item_k[kItemCap];  // key kind: 0 = z, 1 = Gumbel
   float item_e[kItemCap];  // expected run key (NaN if unknown)
-  uint32_t whole[kMaxChunks / 32];
 };
 
 // Sequential draws run on a wave of their own (the parent's second wave):
@@ -60,14 +59,40 @@ struct DrawLds {
   float lmass;                   // base-2 log of the parent's whole q_T mass (before the draws)
 };
 
-// Workgroup LDS of the merge: four parents of one wave each, or, for
-// sequential draws, one parent of two waves.
-template <bool SEQ>
+// Cooperative merges (few parents, greedy or Gumbel): kCoopWaves waves rescan
+// one parent's candidate runs together, kCoopBatch runs at a time each.
+constexpr int kCoopWaves = 8;
+constexpr int kCoopBatch = 4;
+// The most parents merged so, by mode (a Gumbel merge's chain is twice as
+// long).  ts_expand with one wave each and cooperative, V = 128256, K = 8:
+// Gumbel r = 64 with 384 and 512 parents 64.8, 80.7 and 56.6, 71.8 us, r = 256
+// 103.5, 123.6 and 97.0, 119.3; greedy r = 64 with 16, 128, 256 and 320 parents
+// 18.9, 23.8, 33.5, 38.7 and 17.1, 22.2, 30.5, 40.8.
+__host__ __device__ constexpr int coop_parents(int mode) { return mode == kModeGumbel ? 512 : 256; }
+// What the waves of a cooperative merge leave for the scoring wave: the
+// entries of their lists by kind (z, Gumbel), in any order, and the list in order.
+struct CoopLds {
+  float val[2][kCoopWaves * TS_MAX_K], aux[2][kCoopWaves * TS_MAX_K];
+  int id[2][kCoopWaves * TS_MAX_K];
+  float sval[2][TS_MAX_K], saux[2][TS_MAX_K];
+  int sid[2][TS_MAX_K];
+  int cnt[2], mism;
+  float lse0, lseT;
+};
+
+// Workgroup LDS of the merge: parents of one wave each or one parent of all
+// waves (cooperative), or, for sequential draws, one parent of two waves.
+template <bool SEQ, bool COOP>
 struct MergeShared {
   MergeLds l[4];
 };
 template <>
-struct MergeShared<true> {
+struct MergeShared<false, true> {
+  MergeLds l[kCoopWaves];
+  CoopLds co;
+};
+template <>
+struct MergeShared<true, false> {
   MergeLds l[1];
   DrawLds d;
 };
@@ -142,19 +167,19 @@ __device__ __forceinline__ void u_seeds4(const float* p, float (&u)[4]) {
   for (int e = 0; e < 4; ++e) u[e] = v[e];
 }
 
-// Recompute up to kBatch runs of 16 tokens [t, t+16) for one parent with the
+// Recompute up to BATCH runs of 16 tokens [t, t+16) for one parent with the
 // MFMA sequence of pass 1 (same operands in the same K positions, same
 // accumulator start), so the values are bit-identical to the streaming pass.
 // The parent sits in column 0; lanes 0, 16, 32, 48 get tokens t + g*4 + [0,4).
 // Runs of kind 1 also get their Gumbel keys.  All lanes then check the keys
 // against the kind's threshold; candidates go into the kind's list.  A run
 // whose expected maximum is known counts a mismatch if the recomputed one differs.
-template <typename TE, int KS, bool SAMPLE, int PARTS>
+template <typename TE, int KS, bool SAMPLE, int BATCH, int PARTS>
 __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* urow,
                                              const typename Frag<TE>::type (&bcol)[KS],
                                              uint32_t pc1, uint32_t pc2, uint32_t pc3,
-                                             const int (&t)[kBatch], const int (&kind)[kBatch],
-                                             const float (&expect)[kBatch], int nrun,
+                                             const int (&t)[BATCH], const int (&kind)[BATCH],
+                                             const float (&expect)[BATCH], int nrun,
                                              const float (&thr)[2], MergeLds& L, RegList& zl,
                                              RegList& gl, int& mism) {
   typedef Frag<TE> F;
@@ -162,17 +187,17 @@ __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* uro
   const int n = lane & 15, g = lane >> 4;
   const int V = p.V;
   const TE* W2 = static_cast<const TE*>(p.W2);
-  f32x4 acc[kBatch];
+  f32x4 acc[BATCH];
   const uint32_t col0 = opaque_mask(n == 0);
   // whole aligned runs take vector seed loads (uniform over the wave)
   bool vec = sizeof(TE) == 4 || (V & 3) == 0;
 #pragma unroll
-  for (int b = 0; b < kBatch; ++b) {
+  for (int b = 0; b < BATCH; ++b) {
     const int tb = b < nrun ? t[b] : 0;
     vec = vec && (tb & 3) == 0 && tb + 16 <= V;
   }
   // in PARTS parts: all loads of a part first (one round trip), then its MFMAs
-  constexpr int kHalf = kBatch / PARTS;
+  constexpr int kHalf = BATCH / PARTS;
 #pragma unroll
   for (int h = 0; h < PARTS; ++h) {
     typename F::type wf[kHalf][KS];
@@ -207,7 +232,7 @@ __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* uro
   }
   if (n == 0) {
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
+    for (int b = 0; b < BATCH; ++b) {
       const int tb = b < nrun ? t[b] : 0;
       float k4[4];
 #pragma unroll
@@ -236,14 +261,14 @@ __device__ __forceinline__ void rescan_batch(const MergeParams& p, const TE* uro
 #endif
   // lane l checks key j = l + 64 h of the batch (run j / 16, token j % 16)
 #pragma unroll
-  for (int h = 0; h < kBatch / 4; ++h) {
+  for (int h = 0; h < BATCH / 4; ++h) {
     const int j = lane + 64 * h;
     const int b = j >> 4, e = j & 15;
     const float kv = L.bk[b][e];
     int tb = 0, kd = 0;
     float ex = 0.0f;
 #pragma unroll
-    for (int q = 0; q < kBatch; ++q)
+    for (int q = 0; q < BATCH; ++q)
       if (q == b) { tb = t[q]; kd = kind[q]; ex = expect[q]; }
     const bool live = b < nrun && tb + e < V;
     float rm = live ? kv : kNegInf;
@@ -345,6 +370,73 @@ __device__ __forceinline__ float wave_kth_largest(const float (&v)[NE], int K) {
   return r;
 }
 
+// a (descending, in every lane of a group) and its partner group's b into the
+// 2 M of both, descending: a followed by b reversed is a bitonic sequence.
+template <int M>
+__device__ __forceinline__ void merge_all(const float (&a)[M], const float (&b)[M], float (&o)[2 * M]) {
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    o[k] = a[k];
+    o[M + k] = b[M - 1 - k];
+  }
+#pragma unroll
+  for (int j = M; j > 0; j >>= 1)
+#pragma unroll
+    for (int i = 0; i < 2 * M; ++i) {
+      const int l = i ^ j;
+      if (l > i) {
+        const float hi = fmaxf(o[i], o[l]), lo = fminf(o[i], o[l]);
+        o[i] = hi;
+        o[l] = lo;
+      }
+    }
+}
+
+// The K-th largest of the lanes' largest entries (K <= 16), -inf when fewer
+// than K lanes have a finite one: at most wave_kth_largest, as its K values are
+// entries too, and 200 instructions in place of 460.  Of 1024 entries some 9
+// reach the 8th largest so found, not 8.
+template <int NE>
+__device__ __forceinline__ float wave_kth_lane_max(const float (&v)[NE], int K) {
+  float a1[1] = {v[0]}, b1[1], a2[2], b2[2], a4[4], b4[4], a8[8], b8[8];
+#pragma unroll
+  for (int i = 1; i < NE; ++i) a1[0] = fmaxf(a1[0], v[i]);
+  b1[0] = dpp_f32<0xB1>(a1[0]);
+  merge_all<1>(a1, b1, a2);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) b2[k] = dpp_f32<0x4E>(a2[k]);
+  merge_all<2>(a2, b2, a4);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) b4[k] = dpp_f32<0x141>(a4[k]);
+  merge_all<4>(a4, b4, a8);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) b8[k] = dpp_f32<0x140>(a8[k]);
+  float r = kNegInf;
+  if (K <= 8) {
+    merge_top<8>(a8, b8);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b8[k] = xor16_f32(a8[k]);
+    merge_top<8>(a8, b8);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b8[k] = xor32_f32(a8[k]);
+    merge_top<8>(a8, b8);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) r = k == K - 1 ? a8[k] : r;
+  } else {
+    float a[16], b[16];
+    merge_all<8>(a8, b8, a);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) b[k] = xor16_f32(a[k]);
+    merge_top<16>(a, b);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) b[k] = xor32_f32(a[k]);
+    merge_top<16>(a, b);
+#pragma unroll
+    for (int k = 8; k < 16; ++k) r = k == K - 1 ? a[k] : r;
+  }
+  return r;
+}
+
 // Threshold and candidate items for one key kind.  Let L be the K-th
 // largest recorded run key: those are keys of K distinct runs, whose maxima
 // lie within kRunSlack / 2 units of their keys, so the K-th largest token
@@ -354,7 +446,9 @@ __device__ __forceinline__ float wave_kth_largest(const float (&v)[NE], int K) {
 // runs, or, when the chunk's rest key reaches the threshold too, anywhere in
 // the chunk (a whole-chunk item).
 // NE, NR: recorded-run and chunk-rest slots per lane (NE = 4 NR; S <= 64 NR).
-template <int NE, int NR>
+// LANES (cooperative merges, where a few candidates more cost nothing): L is
+// wave_kth_lane_max, any value up to the K-th largest key being as good.
+template <int NE, int NR, bool LANES>
 __device__ __forceinline__ float select_items_n(const MergeParams& p, const RunSummaryPtr& sm,
                                                 int pidx, int kind, MergeLds& L, int& nitems) {
   constexpr int kEntrySlots = NE, kRestSlots = NR;
@@ -377,19 +471,15 @@ __device__ __forceinline__ float select_items_n(const MergeParams& p, const RunS
 #pragma unroll
   for (int i = 0; i < kRestSlots; ++i) rv[i] = sm.rest[pb + min(i * 64 + lane, S - 1)];
   // fewer than K runs recorded: -inf, every token is a candidate
-  float thr = K <= 8 ? wave_kth_largest<8, kEntrySlots>(live, K) : wave_kth_largest<16, kEntrySlots>(live, K);
+  float thr = LANES    ? wave_kth_lane_max<kEntrySlots>(live, K)
+              : K <= 8 ? wave_kth_largest<8, kEntrySlots>(live, K)
+                       : wave_kth_largest<16, kEntrySlots>(live, K);
   thr = key_lowered(thr, kRunSlack);
 
-  // whole chunks
+  // whole chunks: one bit each
+  uint64_t whole[kRestSlots];
 #pragma unroll
-  for (int i = 0; i < kRestSlots; ++i) {
-    const uint64_t wm = __ballot(rv[i] >= thr);
-    if (lane == 0) {
-      L.whole[2 * i] = (uint32_t)wm;
-      L.whole[2 * i + 1] = (uint32_t)(wm >> 32);
-    }
-  }
-  wave_sync_lds();
+  for (int i = 0; i < kRestSlots; ++i) whole[i] = __ballot(i * 64 + lane < S && rv[i] >= thr);
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   int base = nitems;
   // recorded runs of chunks that are not whole
@@ -398,9 +488,11 @@ __device__ __forceinline__ float select_items_n(const MergeParams& p, const RunS
     const int e = i * 64 + lane;
     const int c = e >> 2;
     const bool in = c < S;
-    const bool wh = in && ((L.whole[c >> 5] >> (c & 31)) & 1u);
-    const bool cand = in && !wh && ev[i] >= thr;
+    // the bits of chunks 16 i to 16 i + 15, whose runs the 64 lanes hold
+    const uint32_t wh = (uint32_t)(whole[i >> 2] >> (16 * (i & 3))) >> (lane >> 2);
+    const bool cand = in && (wh & 1u) == 0u && ev[i] >= thr;
     const uint64_t mask = __ballot(cand);
+    if (mask == 0ull) continue;  // most of the slots
     const int off = base + __popcll(mask & lt);
     if (cand && off < kItemCap) {
       const int run = run_of(ev[i]);
@@ -413,8 +505,9 @@ __device__ __forceinline__ float select_items_n(const MergeParams& p, const RunS
 #pragma unroll
   for (int i = 0; i < kRestSlots; ++i) {
     const int c = i * 64 + lane;
-    const bool cand = c < S && rv[i] >= thr;
-    const uint64_t mask = __ballot(cand);
+    const uint64_t mask = whole[i];
+    if (mask == 0ull) continue;
+    const bool cand = (mask >> lane) & 1ull;
     const int off = base + __popcll(mask & lt);
     if (cand && off < kItemCap) {
       L.item_t[off] = -(c + 1);
@@ -442,10 +535,140 @@ __device__ __forceinline__ float select_items_n(const MergeParams& p, const RunS
   return thr;
 }
 
+template <bool LANES>
 __device__ __forceinline__ float select_items(const MergeParams& p, const RunSummaryPtr& sm,
                                               int pidx, int kind, MergeLds& L, int& nitems) {
-  if (p.S <= 64) return select_items_n<4, 1>(p, sm, pidx, kind, L, nitems);
-  return select_items_n<kMaxChunks * kTopRuns / 64, kMaxChunks / 64>(p, sm, pidx, kind, L, nitems);
+  if (p.S <= 64) return select_items_n<4, 1, LANES>(p, sm, pidx, kind, L, nitems);
+  return select_items_n<kMaxChunks * kTopRuns / 64, kMaxChunks / 64, LANES>(p, sm, pidx, kind, L, nitems);
+}
+
+// The candidate items of a parent, in batches of BATCH runs: this wave
+// rescans batches first, first + every, ... of them.
+template <typename TE, int KS, bool SAMPLE, int BATCH, int PARTS>
+__device__ __forceinline__ void rescan_items(const MergeParams& p, const TE* urow,
+                                             const typename Frag<TE>::type (&bcol)[KS],
+                                             uint32_t pc1, uint32_t pc2, uint32_t pc3, int nitems,
+                                             int first, int every, const float (&thr)[2], MergeLds& L,
+                                             RegList& zl, RegList& gl, int& mism) {
+  const int V = p.V, lane = threadIdx.x & 63;
+  const float nan = __builtin_nanf("");
+  int it = 0, sub = 0, turn = first;
+#pragma unroll 1
+  while (it < nitems) {
+    int qt[BATCH], qk[BATCH];
+    float qe[BATCH];
+#pragma unroll
+    for (int q = 0; q < BATCH; ++q) { qt[q] = 0; qk[q] = 0; qe[q] = nan; }
+    int nr = 0;
+    // the leading single-run items of the batch in one read by all lanes
+    // (lane i reads item it + i); they fill the arrays as the loop below
+    // would, the last one read in slot 0
+    if (sub == 0) {
+      const int cnt = min(BATCH, nitems - it);
+      const int li = it + min(lane, cnt - 1);
+      const int code = L.item_t[li];
+      const int kd = L.item_k[li];
+      const float e = L.item_e[li];
+      const uint64_t whole = __ballot(lane < cnt && code < 0);
+      const int m = whole ? min(cnt, __ffsll((unsigned long long)whole) - 1) : cnt;
+#pragma unroll
+      for (int q = 0; q < BATCH; ++q)
+        if (q < m) {
+          qt[q] = lane_i32(code, m - 1 - q);
+          qk[q] = lane_i32(kd, m - 1 - q);
+          qe[q] = lane_f32(e, m - 1 - q);
+        }
+      nr = m;
+      it += m;
+    }
+#pragma unroll 1
+    while (nr < BATCH && it < nitems) {
+      const int code = L.item_t[it];
+      const int kd = L.item_k[it];
+      int t;
+      float e;
+      if (code < 0) {
+        const int cc = -code - 1;
+        const int cbeg = p.cm.begin(cc);
+        const int nruns = ((min(p.cm.begin(cc + 1), V) - cbeg + 63) / 64) * 4;
+        t = cbeg + (sub >> 2) * 64 + (sub & 3) * 16;
+        e = nan;
+        if (++sub == nruns) { sub = 0; ++it; }
+        if (t >= V) continue;
+      } else {
+        t = code;
+        e = L.item_e[it];
+        ++it;
+      }
+#pragma unroll
+      for (int q = BATCH - 1; q > 0; --q) { qt[q] = qt[q - 1]; qk[q] = qk[q - 1]; qe[q] = qe[q - 1]; }
+      qt[0] = t;
+      qk[0] = kd;
+      qe[0] = e;
+      ++nr;
+    }
+    // the batches are dealt out in turn
+    const bool mine = turn == 0;
+    turn = turn == 0 ? every - 1 : turn - 1;
+    if (nr > 0 && mine)
+      rescan_batch<TE, KS, SAMPLE, BATCH, PARTS>(p, urow, bcol, pc1, pc2, pc3, qt, qk, qe, nr, thr, L, zl, gl, mism);
+  }
+}
+
+// The lists of a cooperative merge's waves into one list of each kind, in
+// wave 0's zl and gl (order: key desc, token asc; tokens are distinct, so the
+// result does not depend on the order in which the waves arrive).
+template <bool GUMBEL>
+__device__ __forceinline__ void coop_lists(MergeShared<false, true>& sh, int K, RegList& zl, RegList& gl, int& mism,
+                                           float& lse0, float& lseT) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int kd = GUMBEL ? wv & 1 : 0;
+  const RegList& mine = kd ? gl : zl;
+  CoopLds& co = sh.co;
+  int off = 0;
+  if (lane == 0) {
+    off = atomicAdd(&co.cnt[kd], mine.cnt);
+    if (mism) atomicAdd(&co.mism, mism);
+    if (wv == kCoopWaves - 1) {
+      co.lse0 = lse0;
+      co.lseT = lseT;
+    }
+  }
+  off = lane_i32(off, 0);
+  if (lane < mine.cnt) {
+    co.val[kd][off + lane] = mine.val;
+    co.aux[kd][off + lane] = mine.aux;
+    co.id[kd][off + lane] = mine.id;
+  }
+  __syncthreads();
+  if (wv != 0) return;
+  lse0 = co.lse0;
+  lseT = co.lseT;
+  mism = co.mism;
+#pragma unroll
+  for (int k = 0; k < (GUMBEL ? 2 : 1); ++k) {
+    const int n = co.cnt[k];
+    for (int e = lane; e < n; e += 64) {
+      const float v = co.val[k][e];
+      const int id = co.id[k][e];
+      int at = 0;
+      for (int i = 0; i < n; ++i) at += run_before(co.val[k][i], co.id[k][i], v, id) ? 1 : 0;
+      if (at < K) {
+        co.sval[k][at] = v;
+        co.sid[k][at] = id;
+        co.saux[k][at] = co.aux[k][e];
+      }
+    }
+    wave_sync_lds();
+    RegList& l = k ? gl : zl;
+    reglist_init(l);
+    l.cnt = min(n, K);
+    if (lane < l.cnt) {
+      l.val = co.sval[k][lane];
+      l.id = co.sid[k][lane];
+      l.aux = co.saux[k][lane];
+    }
+  }
 }
 
 // ---------------------------------------------------------------- sequential draws
@@ -727,8 +950,21 @@ __device__ __forceinline__ void seq_draws(const MergeParams& p, int pidx, const 
     seq_draws_n<TE, KS, kSegSlots>(p, pidx, urow, erow_all, pc1, pc2, pc3, L, gl);
 }
 
-template <typename TE, int KS, int MODE>
-__global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) {
+// Greedy and Gumbel merges take one wave per parent, or, for at most
+// coop_parents(MODE) parents (workgroups of kCoopWaves waves), all waves of a
+// workgroup: each finds the threshold for itself, the batches of candidate runs
+// are dealt out over the waves (with Gumbel draws even waves rescan for z, odd
+// ones for the Gumbel keys), and wave 0 puts their lists together.  One wave
+// alone walks a chain of round trips to the candidates' rows with nothing to
+// hide it.  Sequential draws take two waves: rescans and scoring, and the draws.
+//
+// COOP: the kernel of cooperative launches, which also takes one parent per wave
+// where the device holds a larger count.  The other launches keep a kernel of
+// their own: this one's workgroups leave a wave at most 256 registers, which
+// cost the merge of 512 parents at r = 256, K = 16 3 of 82 us in spills.
+template <typename TE, int KS, int MODE, bool COOP>
+__global__ __launch_bounds__(COOP ? 64 * kCoopWaves : MODE == kModeSeq ? 128 : 256) void expand_merge_kernel(const MergeParams p) {
+  static_assert(!(COOP && MODE == kModeSeq), "sequential draws: two waves per parent");
   typedef Frag<TE> F;
   typedef typename F::type FT;
   constexpr bool SAMPLE = MODE != kModeGreedy;
@@ -736,12 +972,15 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
   constexpr bool SEQ = MODE == kModeSeq;
   // Sequential draws: one parent per workgroup; wave 1 draws while wave 0
   // finds the greedy top-K, then wave 0 scores the children.
-  __shared__ MergeShared<SEQ> sh;
+  __shared__ MergeShared<SEQ, COOP> sh;
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
   const int n = lane & 15, g = lane >> 4;
-  const int pidx = SEQ ? blockIdx.x : blockIdx.x * 4 + wv;
-  if (pidx >= launch_parents(p)) return;  // uniform over the workgroup when SEQ
+  const int nparents = launch_parents(p);
+  constexpr int wpw = COOP ? kCoopWaves : SEQ ? 2 : 4;  // waves of the workgroup
+  const bool coop = COOP && nparents <= coop_parents(MODE);
+  const int pidx = SEQ || coop ? blockIdx.x : blockIdx.x * wpw + wv;
+  if (pidx >= nparents) return;  // uniform over the workgroup when SEQ or cooperative
 #ifdef TS_DEBUG_RUNS
   const long long t_start = clock64();
 #endif
@@ -752,7 +991,7 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
                   par.request >= 0 && par.request < p.R;
   const size_t ob = (size_t)pidx * K;
   if (!ok) {
-    if (SEQ && wv != 0) return;
+    if ((SEQ || coop) && wv != 0) return;
     const float nan = __builtin_nanf("");
     if (lane < K) {
       p.out.child_token[ob + lane] = -1;
@@ -808,7 +1047,17 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
   constexpr bool kPartsT = SAMPLE && !SEQ;  // the streaming pass kept sums of z / T
   const bool parts0 = !SEQ || p.need_T;     // ... and sums of z
   float lse0 = __builtin_nanf(""), lseT = __builtin_nanf("");
-  if (parts0) {
+  if constexpr (COOP) {
+    if (coop) {
+      if (threadIdx.x == 0) {
+        sh.co.cnt[0] = 0;
+        sh.co.cnt[1] = 0;
+        sh.co.mism = 0;
+      }
+      __syncthreads();
+    }
+  }
+  if (parts0 && (!coop || wv == kCoopWaves - 1)) {  // the last wave: the one with the fewest batches
     float pm[kRestSlots], ps[kRestSlots], pt[kRestSlots];
 #pragma unroll
     for (int i = 0; i < kRestSlots; ++i) {
@@ -840,78 +1089,31 @@ __global__ __launch_bounds__(256) void expand_merge_kernel(const MergeParams p) 
   }
 
   int nitems = 0;
-  float thr[2];
-  thr[0] = select_items(p, p.zs, pidx, 0, L, nitems);
-  thr[1] = kNegInf;
-  if constexpr (GUMBEL) thr[1] = select_items(p, p.gs, pidx, 1, L, nitems);
+  float thr[2] = {kNegInf, kNegInf};
+  if (!(GUMBEL && coop && (wv & 1) == 1)) thr[0] = select_items<COOP>(p, p.zs, pidx, 0, L, nitems);
+  if constexpr (GUMBEL) {
+    if (!(coop && (wv & 1) == 0)) thr[1] = select_items<COOP>(p, p.gs, pidx, 1, L, nitems);
+  }
 
   RegList zl, gl;
   reglist_init(zl);
   reglist_init(gl);
   int mism = 0;
-  const float nan = __builtin_nanf("");
   // a batch's loads in one round trip at rank <= 64; in two with sequential
   // draws (beside the draws, which are the longer chain, the wave keeps to
   // the registers that leave four waves per SIMD) or at higher ranks
   constexpr int kRescanParts = (SEQ || KS > 2) ? 2 : 1;
-  int it = 0, sub = 0;
-#pragma unroll 1
-  while (it < nitems) {
-    int qt[kBatch], qk[kBatch];
-    float qe[kBatch];
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) { qt[q] = 0; qk[q] = 0; qe[q] = nan; }
-    int nr = 0;
-    // the leading single-run items of the batch in one read by all lanes
-    // (lane i reads item it + i); they fill the arrays as the loop below
-    // would, the last one read in slot 0
-    if (sub == 0) {
-      const int cnt = min(kBatch, nitems - it);
-      const int li = it + min(lane, cnt - 1);
-      const int code = L.item_t[li];
-      const int kd = L.item_k[li];
-      const float e = L.item_e[li];
-      const uint64_t whole = __ballot(lane < cnt && code < 0);
-      const int m = whole ? min(cnt, __ffsll((unsigned long long)whole) - 1) : cnt;
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q)
-        if (q < m) {
-          qt[q] = lane_i32(code, m - 1 - q);
-          qk[q] = lane_i32(kd, m - 1 - q);
-          qe[q] = lane_f32(e, m - 1 - q);
-        }
-      nr = m;
-      it += m;
+  if constexpr (COOP) {
+    constexpr int nw = GUMBEL ? kCoopWaves / 2 : kCoopWaves;  // waves of a kind
+    rescan_items<TE, KS, GUMBEL, kCoopBatch, 1>(p, urow, bcol, pc1, pc2, pc3, nitems,
+                                                !coop ? 0 : GUMBEL ? wv >> 1 : wv, coop ? nw : 1, thr, L, zl, gl, mism);
+    if (coop) {
+      coop_lists<GUMBEL>(sh, K, zl, gl, mism, lse0, lseT);
+      if (wv != 0) return;
     }
-#pragma unroll 1
-    while (nr < kBatch && it < nitems) {
-      const int code = L.item_t[it];
-      const int kd = L.item_k[it];
-      int t;
-      float e;
-      if (code < 0) {
-        const int cc = -code - 1;
-        const int cbeg = p.cm.begin(cc);
-        const int nruns = ((min(p.cm.begin(cc + 1), V) - cbeg + 63) / 64) * 4;
-        t = cbeg + (sub >> 2) * 64 + (sub & 3) * 16;
-        e = nan;
-        if (++sub == nruns) { sub = 0; ++it; }
-        if (t >= V) continue;
-      } else {
-        t = code;
-        e = L.item_e[it];
-        ++it;
-      }
-#pragma unroll
-      for (int q = kBatch - 1; q > 0; --q) { qt[q] = qt[q - 1]; qk[q] = qk[q - 1]; qe[q] = qe[q - 1]; }
-      qt[0] = t;
-      qk[0] = kd;
-      qe[0] = e;
-      ++nr;
-    }
-    if (nr > 0)
-      rescan_batch<TE, KS, GUMBEL, kRescanParts>(p, urow, bcol, pc1, pc2, pc3, qt, qk, qe, nr, thr, L, zl, gl,
-                                                 mism);
+  } else {
+    rescan_items<TE, KS, GUMBEL, kBatch, kRescanParts>(p, urow, bcol, pc1, pc2, pc3, nitems, 0, 1, thr, L, zl, gl,
+                                                       mism);
   }
   if constexpr (SEQ) {
     __syncthreads();  // the draws of wave 1

@@ -326,21 +326,27 @@ void launch_eval(const ts_drafter* d, const ExpandParams& p, const Plan& pl, hip
 }
 
 void launch_merge(const ts_drafter* d, const MergeParams& p, const Plan& pl, hipStream_t s) {
-  // one parent per wave; sequential draws: one parent per workgroup of two waves
+  // sequential draws: one parent per workgroup of two waves.  Otherwise one
+  // parent per wave, or per workgroup of kCoopWaves for few parents; where
+  // the device holds the count that kernel takes either form by it, and the
+  // grid covers both.
   const bool seq = pl.mode == kModeSeq;
-  const dim3 grid(seq ? p.P : (p.P + 3) / 4), block(seq ? 128 : 256);
+  const bool coop = !seq && (p.P_dev || p.P <= coop_parents(pl.mode));
+  const int waves = seq ? 2 : coop ? kCoopWaves : 4;
+  const int groups = seq ? p.P : std::max((p.P + waves - 1) / waves, coop ? std::min(p.P, coop_parents(pl.mode)) : 0);
+  const dim3 grid(groups), block(64 * waves);
   if (d->dtype == TS_BF16) {
     switch (pl.ks) {
-      case 1: launch_merge_t<uint16_t, 1>(p, pl.mode, grid, block, s); break;
-      case 2: launch_merge_t<uint16_t, 2>(p, pl.mode, grid, block, s); break;
-      case 4: launch_merge_t<uint16_t, 4>(p, pl.mode, grid, block, s); break;
-      default: launch_merge_t<uint16_t, 8>(p, pl.mode, grid, block, s); break;
+      case 1: launch_merge_t<uint16_t, 1>(p, pl.mode, coop, grid, block, s); break;
+      case 2: launch_merge_t<uint16_t, 2>(p, pl.mode, coop, grid, block, s); break;
+      case 4: launch_merge_t<uint16_t, 4>(p, pl.mode, coop, grid, block, s); break;
+      default: launch_merge_t<uint16_t, 8>(p, pl.mode, coop, grid, block, s); break;
     }
   } else {
     switch (pl.ks) {
-      case 4: launch_merge_t<float, 4>(p, pl.mode, grid, block, s); break;
-      case 8: launch_merge_t<float, 8>(p, pl.mode, grid, block, s); break;
-      default: launch_merge_t<float, 16>(p, pl.mode, grid, block, s); break;
+      case 4: launch_merge_t<float, 4>(p, pl.mode, coop, grid, block, s); break;
+      case 8: launch_merge_t<float, 8>(p, pl.mode, coop, grid, block, s); break;
+      default: launch_merge_t<float, 16>(p, pl.mode, coop, grid, block, s); break;
     }
   }
 }
