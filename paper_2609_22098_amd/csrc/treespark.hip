@@ -252,10 +252,21 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   const int s_max = std::max(1, std::min((d->V + 255) / 256, store_z && !sizing_only ? INT_MAX : kMaxChunks));
   int S = s_max;
   if (!sizing_only && !max_chunks) {
-    const int concurrent = device_cus() *
-        eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg);
+    // At most four workgroups per CU: the kernels with one parent block per
+    // wave fit five, but filling them all leaves no slack to even out the
+    // chunks and more prologues.  ts_expand, V = 128256, r = 64, planned for five
+    // and for four: 400 greedy parents 51.2 and 42.5 us, 320 38.1 and 34.4;
+    // sequential draws T = 0.7, 384 parents 56.2 and 46.5, 450 63.8 and 52.5.
+    const int fit = eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg);
+    const int concurrent = device_cus() * (store_z ? fit : std::min(fit, 4));
     const int rounds = std::max(1, (pl.n_pgroups * s_min + concurrent - 1) / concurrent);
     S = std::max(1, rounds * concurrent / pl.n_pgroups);
+    // Chunks are dealt to the 8 XCDs in turn, all parent groups of one to the
+    // same XCD: with S no multiple of 8 some XCDs get one chunk more and, when
+    // the groups do not divide their share, more workgroups than fit them (600
+    // greedy parents: 170 chunks x 3 groups put 66 on two XCDs that hold 64;
+    // ts_expand 56.9 us, with 168 chunks 49.9).
+    if (S > 8 && !even_chunks && S < s_max) S &= ~7;
     if (even_chunks) {
       // chunks of one rounded-up length: fewer of them
       const int quantum = lds ? 256 : 64;
