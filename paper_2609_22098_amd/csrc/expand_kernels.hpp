@@ -314,31 +314,33 @@ __device__ __forceinline__ void top_store(const RunSummaryPtr& d, size_t o, cons
 // Base-2 log of the q_T mass of this step's 64-token block for the lane's
 // parent: a is the lane's run sum relative to 2^ml; the four lane groups of a
 // parent (lanes n, n+16, n+32, n+48) hold the block's four runs.
-// sum over j of 2^(v[j] * c - ref), as four interleaved partial sums
-// (short dependency chains), combined in a fixed order.
-__device__ __forceinline__ float sum16_exp2(const float (&v)[16], float c, float ref) {
+// sum over j of 2^(v[j] * c + nref), as four interleaved partial sums
+// (short dependency chains), combined in a fixed order.  The reference comes
+// negated: an FMA without a sign modifier and with a literal scale has a short
+// encoding (2.6 cycles of issue per wave, the long one 4.3).
+__device__ __forceinline__ float sum16_exp2(const float (&v)[16], float c, float nref) {
   float a[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) a[q] = exp2_fast(__builtin_fmaf(v[q], c, -ref));
+  for (int q = 0; q < 4; ++q) a[q] = exp2_fast(__builtin_fmaf(v[q], c, nref));
 #pragma unroll
-  for (int j = 4; j < 16; ++j) a[j & 3] += exp2_fast(__builtin_fmaf(v[j], c, -ref));
+  for (int j = 4; j < 16; ++j) a[j & 3] += exp2_fast(__builtin_fmaf(v[j], c, nref));
   return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-// The two sums of one run (scales c0, c1; references r0, r1) interleaved:
+// The two sums of one run (scales c0, c1; negated references n0, n1) interleaved:
 // eight independent chains, each summed in the order of sum16_exp2.
-__device__ __forceinline__ void sum16_exp2_x2(const float (&v)[16], float c0, float r0, float c1, float r1,
+__device__ __forceinline__ void sum16_exp2_x2(const float (&v)[16], float c0, float n0, float c1, float n1,
                                               float& s0, float& s1) {
   float a[4], b[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    a[q] = exp2_fast(__builtin_fmaf(v[q], c0, -r0));
-    b[q] = exp2_fast(__builtin_fmaf(v[q], c1, -r1));
+    a[q] = exp2_fast(__builtin_fmaf(v[q], c0, n0));
+    b[q] = exp2_fast(__builtin_fmaf(v[q], c1, n1));
   }
 #pragma unroll
   for (int j = 4; j < 16; ++j) {
-    a[j & 3] += exp2_fast(__builtin_fmaf(v[j], c0, -r0));
-    b[j & 3] += exp2_fast(__builtin_fmaf(v[j], c1, -r1));
+    a[j & 3] += exp2_fast(__builtin_fmaf(v[j], c0, n0));
+    b[j & 3] += exp2_fast(__builtin_fmaf(v[j], c1, n1));
   }
   s0 = (a[0] + a[1]) + (a[2] + a[3]);
   s1 = (b[0] + b[1]) + (b[2] + b[3]);
@@ -514,13 +516,13 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
       const bool run_high = bref > m0c;
       const float gap = -__builtin_fabsf(m0c - bref);
       const float bl = bref * kLog2e;
-      float a0 = sum16_exp2(v, kLog2e, bl);
+      float a0 = sum16_exp2(v, kLog2e, -bl);
       const float f0 = exp2_fast(gap * kLog2e);
       s0[nb] = run_high ? __builtin_fmaf(s0[nb], f0, a0) : __builtin_fmaf(a0, f0, s0[nb]);
       const float blT = bref * p.cT;
       float aT = 0.0f;
       if (SAMPLE && p.need_T) {
-        aT = sum16_exp2(v, p.cT, blT);
+        aT = sum16_exp2(v, p.cT, -blT);
         const float fT = exp2_fast(gap * p.cT);
         sT[nb] = run_high ? __builtin_fmaf(sT[nb], fT, aT) : __builtin_fmaf(aT, fT, sT[nb]);
       }
@@ -767,6 +769,10 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   const uint16_t* E = static_cast<const uint16_t*>(p.E);
   const uint16_t* W2 = static_cast<const uint16_t*>(p.W2);
   const int V = p.V, r = p.r;
+  // -cT in a register of its own: as a sign modifier it would keep the keys'
+  // FMA in the long encoding
+  float neg_cT = -p.cT;
+  asm("" : "+s"(neg_cT));
 
   // Byte offsets of this lane's U pieces from the step's first token of row
   // 0: its parent's row plus its lane group's 16 tokens (U is under 4 GiB).
@@ -807,11 +813,11 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(bfrag[nb][kk]));
 
   // Per parent (shared by its four lane groups): the reference of the sums,
-  // in logit units, the level that triggers a raise, and the FMA offsets
-  // reference * log2(e) and reference * cT.  It starts below every finite
+  // in logit units, the level that triggers a raise, and the FMA addends
+  // -reference * log2(e) and -reference * cT.  It starts below every finite
   // logit, so the first run with a finite maximum raises it before any term
   // is summed.
-  float ref[NB], lim[NB], off0[NB], offT[NB], s0[NB], sT[NB];
+  float ref[NB], lim[NB], noff0[NB], noffT[NB], s0[NB], sT[NB];
   RunTop zt[NB], gt[NB];
   // sequential draws: the q_T sum of the lane's run j of the open quad, as
   // qx * 2^qr with qr the run maximum times c (c = cT, or log2(e) at T = 1)
@@ -831,7 +837,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     ref[nb] = -1e30f; lim[nb] = -1e30f;
-    off0[nb] = -1e30f * kLog2e; offT[nb] = -1e30f * p.cT;
+    noff0[nb] = 1e30f * kLog2e; noffT[nb] = 1e30f * p.cT;
     s0[nb] = 0.0f; sT[nb] = 0.0f;
     top_init(zt[nb]);
     top_init(gt[nb]);
@@ -938,8 +944,8 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     if constexpr (SUMT) sT[nb] *= exp2_fast(d * p.cT);
     ref[nb] = nr;
     lim[nb] = nr + p.hr;
-    off0[nb] = nr * kLog2e;
-    offT[nb] = nr * p.cT;
+    noff0[nb] = -nr * kLog2e;
+    noffT[nb] = -nr * p.cT;
   };
 
   // z of the parents of block nb for one step: the accumulator starts at U
@@ -987,14 +993,14 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       // the run's q_T sum against its own maximum (finite: an all -inf run sums to 0)
       br = max2_med3(bm, -1e30f) * cX;
       if constexpr (NT)
-        sum16_exp2_x2(v, kLog2e, off0[nb], p.cT, br, a0, ax);
+        sum16_exp2_x2(v, kLog2e, noff0[nb], p.cT, -br, a0, ax);
       else
-        ax = sum16_exp2(v, kLog2e, br);
+        ax = sum16_exp2(v, kLog2e, -br);
     } else {
       if constexpr (SUMT)
-        sum16_exp2_x2(v, kLog2e, off0[nb], p.cT, offT[nb], a0, ax);
+        sum16_exp2_x2(v, kLog2e, noff0[nb], p.cT, noffT[nb], a0, ax);
       else
-        a0 = sum16_exp2(v, kLog2e, off0[nb]);
+        a0 = sum16_exp2(v, kLog2e, noff0[nb]);
     }
     return bm;
   };
