@@ -413,11 +413,29 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
   const int V = p.V, r = p.r;
   const bool vec_ok = sizeof(TE) == 4 || V % 8 == 0;  // 2-byte rows: only at 16-byte boundaries
 
+  const int tbeg = p.cm.begin(chunk);
+  const int tend = min(p.cm.begin(chunk + 1), V);
+  // The first loads leave in the order in which their addresses are known: W2,
+  // the parents, their U, their E rows.
+  // A: row n of M-block bb is token t0 + (n/4)*16 + bb*4 + n%4, so that the
+  // C layout gives lane group g the 16 contiguous tokens t0 + g*16 + [0,16).
+  auto load_a = [&](FT (&afrag)[4][KS], int t0) {
+#pragma unroll
+    for (int bb = 0; bb < 4; ++bb) {
+      const int tA = min(t0 + (n >> 2) * 16 + bb * 4 + (n & 3), V - 1);
+      F::load_row(W2 + (size_t)tA * r, g, afrag[bb]);
+    }
+  };
+
+  URun<TE> ua[NB], ub[NB];
+  FT aa[4][KS], ab[4][KS];
+  load_a(aa, tbeg);
+
   // Per-column parent state (this lane's parent in each of the NB blocks).
   const TE* urow[NB];
   FT bfrag[NB][KS];
   uint32_t pc1[NB], pc2[NB], pc3[NB];
-  int pidx[NB];
+  int pidx[NB], ptok[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     pidx[nb] = (pb * NB + nb) * 16 + n;
@@ -431,18 +449,29 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
       }
     }
     urow[nb] = U + ((size_t)req * p.D + dep) * (size_t)V;
-    const TE* erow = E + (size_t)tok * r;
-    F::load_row(erow, g, bfrag[nb]);
+    ptok[nb] = tok;
     pc1[nb] = (uint32_t)path;
     pc2[nb] = (uint32_t)(path >> 32);
     pc3[nb] = counter_word3(req, dep, 1u);
   }
 
+  auto load_u = [&](URun<TE> (&u)[NB], int t0) {
+    if (vec_ok && t0 + 64 <= V) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) u[nb].load(urow[nb], t0 + g * 16);
+    } else {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) u[nb].load_masked(urow[nb], t0 + g * 16, V);
+    }
+  };
+
+  load_u(ua, tbeg);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) F::load_row(E + (size_t)ptok[nb] * r, g, bfrag[nb]);
+
   float m0[NB], s0[NB], sT[NB];
   RunTop zt[NB], gt[NB];
   BlkWindow bw[NB];
-  const int tbeg = p.cm.begin(chunk);
-  const int tend = min(p.cm.begin(chunk + 1), V);
   const int bfirst = tbeg >> 6;
   const int blast = (tend - 1) >> 6;
 #pragma unroll
@@ -454,16 +483,6 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 
   // One 64-token step: 16 tokens per lane group, each lane owns one parent
   // per block.  u holds this step's U values (prefetched one step ahead).
-  // A: row n of M-block bb is token t0 + (n/4)*16 + bb*4 + n%4, so that the
-  // C layout gives lane group g the 16 contiguous tokens t0 + g*16 + [0,16).
-  auto load_a = [&](FT (&afrag)[4][KS], int t0) {
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb) {
-      const int tA = min(t0 + (n >> 2) * 16 + bb * 4 + (n & 3), V - 1);
-      F::load_row(W2 + (size_t)tA * r, g, afrag[bb]);
-    }
-  };
-
   auto do_step = [&](const URun<TE> (&u)[NB], const FT (&afrag)[4][KS], int t0, int step) {
     f32x4 acc[4][NB];
 #pragma unroll
@@ -554,23 +573,9 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
     }
   };
 
-  auto load_u = [&](URun<TE> (&u)[NB], int t0) {
-    if (vec_ok && t0 + 64 <= V) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) u[nb].load(urow[nb], t0 + g * 16);
-    } else {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) u[nb].load_masked(urow[nb], t0 + g * 16, V);
-    }
-  };
-
   // Steps alternate between two buffers of U values and W2 fragments: the
   // next step's loads are in flight while the current step computes.
-  URun<TE> ua[NB], ub[NB];
-  FT aa[4][KS], ab[4][KS];
   int t0 = tbeg, step = 0;
-  load_u(ua, t0);
-  load_a(aa, t0);
   for (;;) {
     const bool more1 = t0 + 64 < tend;
     if (more1) { load_u(ub, t0 + 64); load_a(ab, t0 + 64); }
@@ -774,6 +779,34 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   float neg_cT = -p.cT;
   asm("" : "+s"(neg_cT));
 
+  const int tbeg = p.cm.begin(chunk);
+  const int tend = min(p.cm.begin(chunk + 1), V);
+  // The first loads leave in the order in which their addresses are known (the
+  // W2 tile, the parents, their U pieces, their E rows), so that a wave starts
+  // after two round trips: with E before the tiles it took three, and a step
+  // of one request's tree is little else.
+  // W2: this wave loads pieces (wv*KS + j)*64 + lane of the tile: row
+  // (n >> 2)*16 + bb*4 + (n & 3) of the step, 16 bytes at k = kk*32 + g*8.
+  // U: tokens t0 + g*16 + 8h + [0, 8) of this lane's parent in block nb.
+  // Both are raw buffer loads: a per-lane byte offset fixed for the whole
+  // chunk plus a scalar offset per step, so a step's loads cost no vector
+  // instruction.  Rows past the vocabulary read as zeros (W2, U's last row)
+  // or as the next row's first tokens (U): the last step masks them.
+  uint32_t woff[KS];
+#pragma unroll
+  for (int j = 0; j < KS; ++j) {
+    const int bb = ((wv & 3) * KS + j) / KS, kk = ((wv & 3) * KS + j) % KS;
+    woff[j] = (uint32_t)((((n >> 2) * 16 + bb * 4 + (n & 3)) * r + kk * 32 + g * 8) * 2);
+  }
+  const u32x4 wsrc = raw_rsrc(W2, (uint32_t)V * r * 2);
+  auto issue_w = [&](u32x4* wb, int t0) {
+    if (wv < 4) {
+#pragma unroll
+      for (int j = 0; j < KS; ++j) lds_buf16_asm(wsrc, woff[j], t0 * r * 2, wb + (wv * KS + j) * 64);
+    }
+  };
+  issue_w(w0, tbeg);
+
   // Byte offsets of this lane's U pieces from the step's first token of row
   // 0: its parent's row plus its lane group's 16 tokens (U is under 4 GiB).
   // A step's loads add them to a scalar base.
@@ -781,32 +814,46 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   uint32_t ush[NB];  // RAG: bits the run's words are shifted by, 0 or 16
   FT bfrag[NB][KS];
   uint32_t pc1[NB], pc2[NB], pc3[NB];
-  int pidx[NB];
+  int pidx[NB], ptok[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     pidx[nb] = (pb * NB + nb) * 16 + n;
-    int tok = 0, dep = 0, req = 0;
-    uint64_t path = 0;
-    if (active && pidx[nb] < P) {
-      const ts_parent par = p.parents[pidx[nb]];
-      if (par.token >= 0 && par.token < V && par.depth >= 0 && par.depth < p.D &&
-          par.request >= 0 && par.request < p.R) {
-        tok = par.token; dep = par.depth; req = par.request; path = par.path;
-      }
-    }
+    // (without branches: the blocks' parents are loaded together)
+    const ts_parent par = p.parents[min(pidx[nb], P - 1)];
+    const bool ok = active & (pidx[nb] < P) & (par.token >= 0) & (par.token < V) & (par.depth >= 0) &
+                    (par.depth < p.D) & (par.request >= 0) & (par.request < p.R);
+    const int tok = ok ? par.token : 0, dep = ok ? par.depth : 0, req = ok ? par.request : 0;
+    const uint64_t path = ok ? par.path : 0ull;
     uoff[nb] = ((uint32_t)(req * p.D + dep) * (uint32_t)V + (uint32_t)g * 16u) * 2u;
     ush[nb] = (uoff[nb] & 2u) << 3;
     if constexpr (RAG) uoff[nb] &= ~3u;
-    const uint16_t* erow = E + (size_t)tok * r;
-    F::load_row(erow, g, bfrag[nb]);
+    ptok[nb] = tok;
     pc1[nb] = (uint32_t)path;
     pc2[nb] = (uint32_t)(path >> 32);
     pc3[nb] = counter_word3(req, dep, 1u);
   }
-  // the E fragments are in registers before the first tile load is queued:
-  // the compiler does not count the queued loads (inline assembly), so its
-  // own waits for these registers inside the loop would otherwise stall on
-  // them
+  // RAG: whole 4-byte words only (with an odd number of elements the array's
+  // last one lies past them: the last step reads it on its own)
+  const u32x4 usrc = raw_rsrc(U, (uint32_t)p.R * p.D * V * 2 & (RAG ? ~3u : ~0u));
+  typedef u32x4 UPieces[NB][2];
+  constexpr int kULoads = RAG ? 3 : 2;  // loads per parent block and step
+  auto issue_u = [&](u32x4* ub, uint32_t* ux, int t0) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) lds_buf16_asm(usrc, uoff[nb], t0 * 2 + 16 * h, ub + wv * kU + (nb * 2 + h) * 64);
+      if constexpr (RAG) lds_buf4_asm(usrc, uoff[nb], t0 * 2 + 32, ux + wv * kX + nb * 64);
+    }
+  };
+  if (active) {
+    issue_u(ub0, ux0, tbeg);
+    if (tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
+  }
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) F::load_row(E + (size_t)ptok[nb] * r, g, bfrag[nb]);
+  // the E fragments are in registers before the first step: the compiler does
+  // not count the queued loads (inline assembly), so its own waits for these
+  // registers inside the loop would otherwise stall on them
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -828,8 +875,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   constexpr bool SUM0 = !SEQ || NT;
   constexpr bool SUMT = NT && !SEQ;
   const float cX = NT ? p.cT : kLog2e;  // scale of the block masses
-  const int tbeg = p.cm.begin(chunk);
-  const int tend = min(p.cm.begin(chunk + 1), V);
   const int bfirst = tbeg >> 6;
   const int blast = (tend - 1) >> 6;
   // the vocabulary's last chunk may write its last window whole (the row is padded to 16 blocks)
@@ -845,39 +890,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     for (int k = 0; k < 4; ++k) { qx[nb][k] = 0.0f; qr[nb][k] = -1e30f; hw[nb][k] = kNegInf; }
   }
 
-  // W2: this wave loads pieces (wv*KS + j)*64 + lane of the tile: row
-  // (n >> 2)*16 + bb*4 + (n & 3) of the step, 16 bytes at k = kk*32 + g*8.
-  // U: tokens t0 + g*16 + 8h + [0, 8) of this lane's parent in block nb.
-  // Both are raw buffer loads: a per-lane byte offset fixed for the whole
-  // chunk plus a scalar offset per step, so a step's loads cost no vector
-  // instruction.  Rows past the vocabulary read as zeros (W2, U's last row)
-  // or as the next row's first tokens (U): the last step masks them.
-  uint32_t woff[KS];
-#pragma unroll
-  for (int j = 0; j < KS; ++j) {
-    const int bb = ((wv & 3) * KS + j) / KS, kk = ((wv & 3) * KS + j) % KS;
-    woff[j] = (uint32_t)((((n >> 2) * 16 + bb * 4 + (n & 3)) * r + kk * 32 + g * 8) * 2);
-  }
-  const u32x4 wsrc = raw_rsrc(W2, (uint32_t)V * r * 2);
-  // RAG: whole 4-byte words only (with an odd number of elements the array's
-  // last one lies past them: the last step reads it on its own)
-  const u32x4 usrc = raw_rsrc(U, (uint32_t)p.R * p.D * V * 2 & (RAG ? ~3u : ~0u));
-  auto issue_w = [&](u32x4* wb, int t0) {
-    if (wv < 4) {
-#pragma unroll
-      for (int j = 0; j < KS; ++j) lds_buf16_asm(wsrc, woff[j], t0 * r * 2, wb + (wv * KS + j) * 64);
-    }
-  };
-  typedef u32x4 UPieces[NB][2];
-  constexpr int kULoads = RAG ? 3 : 2;  // loads per parent block and step
-  auto issue_u = [&](u32x4* ub, uint32_t* ux, int t0) {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) lds_buf16_asm(usrc, uoff[nb], t0 * 2 + 16 * h, ub + wv * kU + (nb * 2 + h) * 64);
-      if constexpr (RAG) lds_buf4_asm(usrc, uoff[nb], t0 * 2 + 32, ux + wv * kX + nb * 64);
-    }
-  };
   // RAG: the run's 16 tokens out of the 9 words at and after its 4-byte boundary
   auto shift_run = [&](UPieces& pu, int nb, uint32_t extra) {
     uint32_t d[9];
@@ -1021,20 +1033,18 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       }
       top_add(zt[nb], run_key(bm, run));
       if constexpr (GUMBEL) {
-        float gm = kNegInf;
+        // the negated keys' minimum, by threes (+inf past the vocabulary)
+        float gm = -kNegInf;
         const uint32_t cbase = (uint32_t)tl >> 2;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           uint32_t c0 = cbase + i, c1 = pc1[nb], c2 = pc2[nb], c3 = pc3[nb];
           philox10(c0, c1, c2, c3, p.keys);
-          const uint32_t w[4] = {c0, c1, c2, c3};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float key = gumbel_key2(v[i * 4 + q], p.cT, w[q]);  // -inf past the vocabulary
-            gm = fmaxf(gm, key);
-          }
+          const float k0 = gumbel_neg_key2(v[i * 4], neg_cT, c0), k1 = gumbel_neg_key2(v[i * 4 + 1], neg_cT, c1);
+          const float k2 = gumbel_neg_key2(v[i * 4 + 2], neg_cT, c2), k3 = gumbel_neg_key2(v[i * 4 + 3], neg_cT, c3);
+          gm = fminf(fminf(fminf(fminf(gm, k0), k1), k2), k3);
         }
-        top_add(gt[nb], run_key(gm, run));
+        top_add(gt[nb], run_key(-gm, run));
       }
     };
     // block by block: block nb + 1's products run on the matrix core while
@@ -1161,11 +1171,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     step = __builtin_amdgcn_readfirstlane(step + 1);
     return true;
   };
-  issue_w(w0, t0);
-  if (active) {
-    issue_u(ub0, ux0, t0);
-    if (t0 + 64 < tend) issue_u(ub1, ux1, t0 + 64);
-  }
   for (;;) {
     if (!do_step(std::integral_constant<int, 0>{})) break;
     if (!do_step(std::integral_constant<int, 1>{})) break;
