@@ -49,12 +49,13 @@ void launch_calib_fit(const float* x, const int32_t* y, const int32_t* sel, int 
 void launch_verify_level(const VerifyPass& vp, bool bf16, int mmax, hipStream_t s);
 // The same level in one launch with register-resident chunks: quads per
 // thread, resident workgroups per CU (0 if unknown), the launch, and the
-// copy of a level's rows out of pinned memory with the clearing of the
-// slots (whole 16-byte pieces of both).
+// copy of a level's rows (and of a second block) out of pinned memory with the
+// clearing of the slots (whole 16-byte pieces of each).
 struct VFused;
 int verify_fused_quads(bool bf16);
 int verify_fused_blocks_per_cu(bool bf16);
 void launch_verify_fused(const VerifyPass& vp, const VFused& f, bool bf16, hipStream_t s);
-void launch_verify_stage_in(const void* src, void* dst, size_t bytes, void* clear, size_t clear_bytes, hipStream_t s);
+void launch_verify_stage_in(const void* src, void* dst, size_t bytes, void* clear, size_t clear_bytes, hipStream_t s,
+                            const void* src2 = nullptr, void* dst2 = nullptr, size_t bytes2 = 0);
 
 }  // namespace ts

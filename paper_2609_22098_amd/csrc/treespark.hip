@@ -1231,12 +1231,15 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
 
   if (T == 0.0f) {
     // Rounds of one argmax launch each: the rows where the walks stand, and
-    // as many levels of their descendants as fit kGreedyBytes (the walks then
-    // go on without another launch).  A launch and its synchronisation cost
-    // about 15 us, in which the GPU reads some 70 MB of rows: reading a few
-    // rows that no walk visits is cheaper than a round more, reading every
-    // row of a large batch is not (64 trees of 64 nodes, V = 151936: 1.3 GB).
-    constexpr size_t kGreedyBytes = 96u << 20, kGreedyRows = 1u << 20;
+    // the levels of their descendants that have at most kGreedyBytes each (the
+    // walks then go on without another launch).  A launch and its
+    // synchronisation cost about 15 us, in which the GPU reads some 70 MB of
+    // rows: reading a level of which only some rows are visited is cheaper than
+    // a round more up to about that size, reading every row of a large batch is
+    // not (64 trees of 64 nodes, V = 151936: 1.3 GB).  64 trees of up to 10
+    // nodes, V = 151936 bf16 and V = 100001 f32: with 96 MB for a round's levels
+    // together 56.7 and 55.4 us, with 72 MB for each 44.3 and 49.7.
+    constexpr size_t kGreedyBytes = 72u << 20, kGreedyRows = 1u << 20;
     const KidIndex& kids = kid_index(tree);  // children of every node in creation order
     const bool bf16 = target_dtype == TS_BF16;
     const size_t row_bytes = (size_t)V * (bf16 ? 2 : 4);
@@ -1249,7 +1252,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
         const size_t end = rows.size();
         size_t more = 0;
         for (size_t i = level; i < end; ++i) more += kids.count(rows[i] / cap, rows[i] % cap);
-        if (more == 0 || (end + more) * row_bytes > kGreedyBytes || end + more > kGreedyRows) break;
+        if (more == 0 || more * row_bytes > kGreedyBytes || end + more > kGreedyRows) break;
         for (size_t i = level; i < end; ++i) {
           const int q = rows[i] / cap, p = rows[i] % cap;
           const int* ch = kids.first(q, p);
@@ -1356,11 +1359,48 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
         if (kids.count(q, ch[j]) > 0) add_node(q, ch[j]);
     }
     const int nn = (int)nodes.size();
+    // the nodes' items and, after them, their children's records
+    int mmax = 0;
+    auto build_items = [&] {
+      VerifyNext* hnext = reinterpret_cast<VerifyNext*>(hitem + nn);
+      for (int i = 0, z = 0; i < nn; ++i) {
+        const int q = nodes[i] / cap;
+        const size_t row = (size_t)q * cap, o = nodes[i];
+        VerifyItem it{};
+        VerifyNext nx{};
+        it.request = q;
+        it.node = nodes[i] % cap;
+        it.depth = tree->depth[o];
+        it.path = tree->path[o];
+        const int* ch = kids.first(q, it.node);
+        it.m = std::min(kids.count(q, it.node), TS_MAX_K);
+        for (int j = 0; j < it.m; ++j) {
+          it.child_tok[j] = tree->token[row + ch[j]];
+          nx.child_node[j] = ch[j];
+          nx.child_path[j] = tree->path[row + ch[j]];
+          nx.child_item[j] = kids.count(q, ch[j]) == 0 ? kNextLeaf : node_at[row + ch[j]];
+        }
+        it.zrow = it.m > 0 ? z++ : -1;
+        mmax = std::max(mmax, it.m);
+        hitem[i] = it;
+        hnext[i] = nx;
+      }
+      for (int o : nodes) node_at[o] = kNextHost;
+    };
+    VerifyItem* ditems = reinterpret_cast<VerifyItem*>(ws + vl.off_items);
+    VerifyNext* dnext = reinterpret_cast<VerifyNext*>(ditems + nn);
+    static_assert(sizeof(VerifyItem) % 8 == 0 && sizeof(VerifyNext) % 8 == 0, "aligned one after the other");
+    const size_t items_bytes = nn * (sizeof(VerifyItem) + sizeof(VerifyNext));
     // Every workgroup of the recompute reads all of its rows' parents: they
     // are copied to the device first, with the clearing (594 workgroups x 64
-    // parents out of pinned memory took it from 22 to 31 us).  The nodes'
-    // items are built and copied while it runs.
-    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), dslots, clear, s);
+    // parents out of pinned memory took it from 22 to 31 us).  The items of a
+    // large round are built and copied while it runs; a small one's, which take
+    // the host a microsecond, go with the parents, a launch less (one request
+    // of 5 nodes, V = 6000: 47.6 us apart, 44.5 together).
+    const bool together = nn <= 32;
+    if (together) build_items();
+    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), dslots, clear, s, hitem, ditems,
+                           together ? items_bytes : 0);
     TS_HIP(hipGetLastError());
     clear = 0;
     if (nz > 0) {
@@ -1369,36 +1409,11 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
                   pl, s);
       TS_HIP(hipGetLastError());
     }
-    VerifyNext* hnext = reinterpret_cast<VerifyNext*>(hitem + nn);
-    int mmax = 0;
-    for (int i = 0, z = 0; i < nn; ++i) {
-      const int q = nodes[i] / cap;
-      const size_t row = (size_t)q * cap, o = nodes[i];
-      VerifyItem it{};
-      VerifyNext nx{};
-      it.request = q;
-      it.node = nodes[i] % cap;
-      it.depth = tree->depth[o];
-      it.path = tree->path[o];
-      const int* ch = kids.first(q, it.node);
-      it.m = std::min(kids.count(q, it.node), TS_MAX_K);
-      for (int j = 0; j < it.m; ++j) {
-        it.child_tok[j] = tree->token[row + ch[j]];
-        nx.child_node[j] = ch[j];
-        nx.child_path[j] = tree->path[row + ch[j]];
-        nx.child_item[j] = kids.count(q, ch[j]) == 0 ? kNextLeaf : node_at[row + ch[j]];
-      }
-      it.zrow = it.m > 0 ? z++ : -1;
-      mmax = std::max(mmax, it.m);
-      hitem[i] = it;
-      hnext[i] = nx;
+    if (!together) {
+      build_items();
+      launch_verify_stage_in(hitem, ditems, items_bytes, nullptr, 0, s);
+      TS_HIP(hipGetLastError());
     }
-    for (int o : nodes) node_at[o] = kNextHost;
-    VerifyItem* ditems = reinterpret_cast<VerifyItem*>(ws + vl.off_items);
-    VerifyNext* dnext = reinterpret_cast<VerifyNext*>(ditems + nn);
-    static_assert(sizeof(VerifyItem) % 8 == 0 && sizeof(VerifyNext) % 8 == 0, "aligned one after the other");
-    launch_verify_stage_in(hitem, ditems, nn * (sizeof(VerifyItem) + sizeof(VerifyNext)), nullptr, 0, s);
-    TS_HIP(hipGetLastError());
     VerifyPass vp{};
     vp.target = target;
     vp.cap = cap;

@@ -70,20 +70,27 @@ void launch_verify_fused(const VerifyPass& vp, const VFused& f, bool bf16, hipSt
     hipLaunchKernelGGL((verify_fused_kernel<float, kFusedQuadsF32>), grid, block, 0, s, VFusedArgs{vp, f});
 }
 
-// Copies n16 16-byte pieces (the first level's rows, from the host's pinned
-// buffer) and clears nclear of them (the level slots).
-__global__ void verify_stage_in_kernel(const u32x4* src, u32x4* dst, int n16, u32x4* clear, int nclear) {
+// Copies n16 16-byte pieces (a round's rows, from the host's pinned buffer) and
+// n16b more (a small round's items), and clears nclear of them (the level slots).
+__global__ void verify_stage_in_kernel(const u32x4* src, u32x4* dst, int n16, const u32x4* src2, u32x4* dst2, int n16b,
+                                       u32x4* clear, int nclear) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n16) dst[i] = src[i];
+  u32x4 a = {}, b = {};
+  if (i < n16) a = src[i];
+  if (i < n16b) b = src2[i];
+  if (i < n16) dst[i] = a;
+  if (i < n16b) dst2[i] = b;
   if (i < nclear) clear[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
-void launch_verify_stage_in(const void* src, void* dst, size_t bytes, void* clear, size_t clear_bytes, hipStream_t s) {
-  const int n16 = (int)((bytes + 15) / 16), nc = (int)((clear_bytes + 15) / 16);
-  const int n = std::max(n16, nc);
+void launch_verify_stage_in(const void* src, void* dst, size_t bytes, void* clear, size_t clear_bytes, hipStream_t s,
+                            const void* src2, void* dst2, size_t bytes2) {
+  const int n16 = (int)((bytes + 15) / 16), n16b = (int)((bytes2 + 15) / 16), nc = (int)((clear_bytes + 15) / 16);
+  const int n = std::max(std::max(n16, n16b), nc);
   if (n > 0)
     hipLaunchKernelGGL(verify_stage_in_kernel, dim3((n + 255) / 256), dim3(256), 0, s, static_cast<const u32x4*>(src),
-                       static_cast<u32x4*>(dst), n16, static_cast<u32x4*>(clear), nc);
+                       static_cast<u32x4*>(dst), n16, static_cast<const u32x4*>(src2), static_cast<u32x4*>(dst2), n16b,
+                       static_cast<u32x4*>(clear), nc);
 }
 
 }  // namespace ts
