@@ -774,10 +774,12 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   const uint16_t* E = static_cast<const uint16_t*>(p.E);
   const uint16_t* W2 = static_cast<const uint16_t*>(p.W2);
   const int V = p.V, r = p.r;
-  // -cT in a register of its own: as a sign modifier it would keep the keys'
-  // FMA in the long encoding
+  // -cT in a vector register of its own: as a sign modifier it would keep the
+  // keys' FMA in the long encoding, and from a scalar register the short one
+  // costs as much (Gumbel T = 0.7, V = 151936, 128 and 2048 parents 38.1 and
+  // 247.4 us, so 37.0 and 245.6)
   float neg_cT = -p.cT;
-  asm("" : "+s"(neg_cT));
+  if constexpr (GUMBEL) asm("" : "+v"(neg_cT));
 
   const int tbeg = p.cm.begin(chunk);
   const int tend = min(p.cm.begin(chunk + 1), V);
