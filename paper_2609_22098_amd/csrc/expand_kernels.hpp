@@ -415,8 +415,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 
   const int tbeg = p.cm.begin(chunk);
   const int tend = min(p.cm.begin(chunk + 1), V);
-  // The first loads leave in the order in which their addresses are known: W2,
-  // the parents, their U, their E rows.
+  // The first loads take two round trips: the parents, then W2, U and E.
   // A: row n of M-block bb is token t0 + (n/4)*16 + bb*4 + n%4, so that the
   // C layout gives lane group g the 16 contiguous tokens t0 + g*16 + [0,16).
   auto load_a = [&](FT (&afrag)[4][KS], int t0) {
@@ -429,7 +428,6 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 
   URun<TE> ua[NB], ub[NB];
   FT aa[4][KS], ab[4][KS];
-  load_a(aa, tbeg);
 
   // Per-column parent state (this lane's parent in each of the NB blocks).
   const TE* urow[NB];
@@ -465,6 +463,7 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
     }
   };
 
+  load_a(aa, tbeg);
   load_u(ua, tbeg);
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) F::load_row(E + (size_t)ptok[nb] * r, g, bfrag[nb]);
@@ -783,10 +782,11 @@ void expand_eval_lds_kernel(const ExpandParams p) {
 
   const int tbeg = p.cm.begin(chunk);
   const int tend = min(p.cm.begin(chunk + 1), V);
-  // The first loads leave in the order in which their addresses are known (the
-  // W2 tile, the parents, their U pieces, their E rows), so that a wave starts
-  // after two round trips: with E before the tiles it took three, and a step
-  // of one request's tree is little else.
+  // The first loads take two round trips: the parents, then the tiles and the
+  // E rows together (E before the tiles made it three: 2048 parents, T = 0.7,
+  // V = 128256 130.3 us in place of 128.0; the W2 tile before the parents, which
+  // then wait for it, as loads return in order: 31 parents, V = 15936, r = 128
+  // 14.8 us in place of 14.6).
   // W2: this wave loads pieces (wv*KS + j)*64 + lane of the tile: row
   // (n >> 2)*16 + bb*4 + (n & 3) of the step, 16 bytes at k = kk*32 + g*8.
   // U: tokens t0 + g*16 + 8h + [0, 8) of this lane's parent in block nb.
@@ -807,7 +807,6 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       for (int j = 0; j < KS; ++j) lds_buf16_asm(wsrc, woff[j], t0 * r * 2, wb + (wv * KS + j) * 64);
     }
   };
-  issue_w(w0, tbeg);
 
   // Byte offsets of this lane's U pieces from the step's first token of row
   // 0: its parent's row plus its lane group's 16 tokens (U is under 4 GiB).
@@ -847,6 +846,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       if constexpr (RAG) lds_buf4_asm(usrc, uoff[nb], t0 * 2 + 32, ux + wv * kX + nb * 64);
     }
   };
+  issue_w(w0, tbeg);
   if (active) {
     issue_u(ub0, ux0, tbeg);
     if (tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
