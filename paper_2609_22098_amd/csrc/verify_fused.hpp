@@ -296,6 +296,9 @@ __device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int level
   f.epoch += (uint32_t)level;
   __syncthreads();  // the walk's place is set, the previous level's readers of the shared records are done
   const int at_node = __builtin_amdgcn_readfirstlane(sh_node);
+  // every lane's own copy: at the walk's end wave 0 reports the path from it
+  uint64_t digits = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sh_digits) |
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(sh_digits >> 32)) << 32);
   if (at_node < 0)  // an accepted leaf: its item is in place
     ;
   else if (tid < kItemWords)
@@ -541,8 +544,9 @@ __device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int level
   if (took) {
     const int s = __builtin_amdgcn_readfirstlane(rec.stage) - 1;
     const int ci = __builtin_amdgcn_readfirstlane(snext.child_item[s]);
+    digits |= (uint64_t)s << (4 * level);
     if (tid == 0) {
-      sh_digits |= (uint64_t)s << (4 * level);
+      sh_digits = digits;
       sh_node = ci;  // >= 0, or set below
     }
     // the accepted child's logits are there: the walk goes on at it (a walk
@@ -578,7 +582,7 @@ __device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int level
       if (tid < kDoneWords) {
         const uint32_t v = tid == kDoneBonus ? (uint32_t)id
                            : tid == kDoneState ? (uint32_t)accepted | (ended ? kDoneEnded : 0u)
-                                               : (uint32_t)(sh_digits >> (32 * (tid - kDonePath)));
+                                               : (uint32_t)(digits >> (32 * (tid - kDonePath)));
         __hip_atomic_store(f.done + (size_t)it * kDoneWords + tid, ((uint64_t)epoch0 << 32) | v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
       }
