@@ -59,6 +59,10 @@ struct DrainOnError {
   }
 };
 
+// Polls of one wait of a one-launch verification round before it gives up (a
+// poll takes about a microsecond).
+constexpr int kFusedSpinLimit = 1 << 16;
+
 // Page-locked host staging for the small transfers of the host loops, so that
 // they are true asynchronous DMA copies (kernels also read and write parts of
 // it directly).  It belongs to the calling host thread, grows on demand and
@@ -74,6 +78,7 @@ struct ThreadState {
   // per-stage launches after a wait ran out, and run per stage from the start
   int64_t fused_levels = 0, fused_fallbacks = 0, staged_levels = 0;
   int32_t verify_mode = TS_VERIFY_AUTO;
+  int32_t wait_limit = kFusedSpinLimit;
 };
 ThreadState& thread_state() {
   thread_local ThreadState st;
@@ -744,8 +749,6 @@ struct FusedPlan {
   bool ok;
   int cpi, chunk;
 };
-// Polls of one wait before it gives up (a poll takes about a microsecond).
-constexpr int kFusedSpinLimit = 1 << 16;
 // Workgroups of a one-launch level that the device holds at once, the most
 // such a launch has (its slots beyond them are never used, nor cleared).
 long long fused_capacity(bool bf16) { return (long long)std::max(verify_fused_blocks_per_cu(bf16), 0) * device_cus(); }
@@ -902,6 +905,12 @@ int32_t ts_verify_set_mode(int32_t mode) {
   thread_state().verify_mode = mode;
   return TS_OK;
 }
+
+// Not part of the ABI: the calling thread's limit on the polls of one wait
+// between the workgroups of a verification round, for the tests of the way
+// back to the per-stage launches (0: every wait gives up at once; negative:
+// the default).  Every kernel still runs to its end.
+void ts_internal_verify_wait_limit(int32_t polls) { thread_state().wait_limit = polls < 0 ? kFusedSpinLimit : polls; }
 
 int32_t ts_verify_level_counts(int64_t* fused, int64_t* fallbacks, int64_t* staged) {
   g_last_error.clear();
@@ -1332,7 +1341,11 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   uint64_t* dslots = reinterpret_cast<uint64_t*>(ws + vl.off_sync);
   const size_t nslots = std::min<size_t>(fused_slot_words(R), 2 * kSlotWords * fused_capacity(bf16));
   int* derr = reinterpret_cast<int*>(dslots + nslots);
-  size_t clear = nslots * 8 + 4;  // bytes to clear before the first launch
+  // cleared before the first launch; before the others the flag alone: a wait
+  // can run out beside a walk that still completes, and a flag left over would
+  // end the next launch's waits with nothing to tell the host
+  void* clear_at = dslots;
+  size_t clear = nslots * 8 + 4;
   uint32_t epoch = 1;
   std::vector<int> next, nodes, node_at((size_t)R * cap, kNextHost);
   while (!active.empty()) {
@@ -1399,10 +1412,11 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     // of 5 nodes, V = 6000: 47.6 us apart, 44.5 together).
     const bool together = nn <= 32;
     if (together) build_items();
-    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), dslots, clear, s, hitem, ditems,
+    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), clear_at, clear, s, hitem, ditems,
                            together ? items_bytes : 0);
     TS_HIP(hipGetLastError());
-    clear = 0;
+    clear_at = derr;
+    clear = 4;
     if (nz > 0) {
       const Plan pl = make_plan(d, nz, T, TS_SAMPLER_GUMBEL, true);
       launch_eval(d, eval_params(d, reinterpret_cast<const ts_parent*>(ws + vl.off_par), nz, T, seed, pl, nullptr, zbuf),
@@ -1444,7 +1458,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       f.epoch = epoch;
       f.err = derr;
       f.herr = const_cast<int32_t*>(herr);
-      f.spin_limit = kFusedSpinLimit;
+      f.spin_limit = thread_state().wait_limit;
       f.next = dnext;
       f.done = done;
       std::fill(done, done + (size_t)ni * kDoneWords, 0ull);
@@ -1457,7 +1471,6 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       if (failed) {
         ++thread_state().fused_levels;
         ++thread_state().fused_fallbacks;
-        launch_verify_stage_in(nullptr, nullptr, 0, derr, 4, s);
         staged = true;
       }
     } else {

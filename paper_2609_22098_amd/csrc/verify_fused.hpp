@@ -61,7 +61,7 @@ struct VFused {
   uint32_t epoch;    // the first level's tag, the next levels count on (slots start the call at zero)
   int* err;          // device flag: a wait ran out
   int32_t* herr;     // the flag's pinned host copy
-  int spin_limit;    // polls before a wait gives up
+  int spin_limit;    // polls before a wait gives up (0: no wait is begun)
   const VerifyNext* next;  // of the launch's nodes, as vp.items
   uint64_t* done;    // [nitems][kDoneWords], pinned host memory: the items' results, zero before the launch
 };
@@ -186,7 +186,14 @@ __device__ __forceinline__ bool poll_slots(const VFused& f, int it, int w0, uint
   bool ready = !mine;
 #pragma unroll
   for (int i = 0; i < NW; ++i) out[i] = 0u;
-  for (int n = 1;; ++n) {
+  for (int n = 0;; ++n) {
+    if (n >= f.spin_limit) {
+      if (lane == 0) {
+        __hip_atomic_store(f.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(f.herr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+      return false;
+    }
     if (!ready) {
       uint64_t v[NW];
 #pragma unroll
@@ -201,16 +208,7 @@ __device__ __forceinline__ bool poll_slots(const VFused& f, int it, int w0, uint
       }
     }
     if (__all(ready)) return true;
-    if ((n & 63) == 0) {
-      if (__hip_atomic_load(f.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-      if (n >= f.spin_limit) {
-        if (lane == 0) {
-          __hip_atomic_store(f.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(f.herr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-        return false;
-      }
-    }
+    if ((n & 63) == 63 && __hip_atomic_load(f.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
     __builtin_amdgcn_s_sleep(1);
   }
 }
