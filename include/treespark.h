@@ -402,13 +402,16 @@ int32_t ts_verify_set_mode(int32_t mode);
 
 /*
  * ts_verify_level_counts: how the T > 0 levels of ts_verify calls on the
- * calling thread ran.  *fused: levels walked inside one launch, each workgroup
- * holding its chunk of the target and draft rows in registers (when every
- * workgroup of the launch can be resident at once; one launch may walk several
- * levels); *fallbacks: of those, the levels run again through the per-stage
- * launches because a wait between workgroups ran out; *staged: levels run through the per-stage launches from
- * the start (pass A, one launch per stage, resolve).  The counts are the
- * thread's totals since its first call (ts_release_thread_state keeps them).
+ * calling thread ran.  A level is a node with children at which a walk tries
+ * them (a tree of its root alone counts as one).  *fused: levels walked inside
+ * one launch, each workgroup holding its chunk of the target and draft rows in
+ * registers (when every workgroup of the launch can be resident at once; one
+ * launch may walk several levels, and counts those of its longest walk);
+ * *fallbacks: of those, the first levels of launches that were given up
+ * because a wait between workgroups ran out, run again through the per-stage
+ * launches; *staged: levels run through the per-stage launches from the start
+ * (pass A, one launch per stage, resolve).  The counts are the thread's totals
+ * since its first call (ts_release_thread_state keeps them).
  * Errors: NULL pointers.
  */
 int32_t ts_verify_level_counts(int64_t* fused, int64_t* fallbacks, int64_t* staged);

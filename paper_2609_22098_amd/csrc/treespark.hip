@@ -1500,7 +1500,8 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
         ended = (state & kDoneEnded) != 0;
         digits = (uint64_t)(uint32_t)w[kDonePath] | ((uint64_t)(uint32_t)w[kDonePath + 1] << 32);
         b = (int32_t)(uint32_t)w[kDoneBonus];
-        levels = std::max(levels, std::max(accepted, 1));
+        // the accepted children's levels and that of the node whose children were all rejected
+        levels = std::max(levels, std::max(accepted + (ended && !(state & kDoneLeaf) ? 1 : 0), 1));
       }
       for (int l = 0; l < accepted; ++l) {
         if (path_len[q] >= TS_MAX_D) {

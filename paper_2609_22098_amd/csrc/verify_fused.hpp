@@ -87,10 +87,11 @@ __device__ __forceinline__ T* as_global(T* p) {
 enum : int {
   kDoneBonus = 0,   // the bonus token
   kDonePath = 1,    // and 2: the accepted children's places in draw order, 4 bits a level
-  kDoneState = 3,   // accepted children | kDoneEnded
+  kDoneState = 3,   // accepted children | kDoneEnded | kDoneLeaf
   kDoneWords = 4
 };
 constexpr uint32_t kDoneEnded = 256;  // the walk has ended (the bonus counts)
+constexpr uint32_t kDoneLeaf = 512;   // at a node without children (no level of its own)
 static_assert(TS_MAX_K <= 16 && TS_MAX_D <= 16, "a level takes 4 bits of two words");
 
 // Quad of target values as loaded: four bf16 in two words, or four floats.
@@ -579,7 +580,7 @@ __device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int level
       const int accepted = level + (took ? 1 : 0);
       if (tid < kDoneWords) {
         const uint32_t v = tid == kDoneBonus ? (uint32_t)id
-                           : tid == kDoneState ? (uint32_t)accepted | (ended ? kDoneEnded : 0u)
+                           : tid == kDoneState ? (uint32_t)accepted | (ended ? kDoneEnded : 0u) | (m == 0 ? kDoneLeaf : 0u)
                                                : (uint32_t)(digits >> (32 * (tid - kDonePath)));
         __hip_atomic_store(f.done + (size_t)it * kDoneWords + tid, ((uint64_t)epoch0 << 32) | v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
