@@ -262,7 +262,11 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
     // chunks and more prologues.  ts_expand, V = 128256, r = 64, planned for five
     // and for four: 400 greedy parents 51.2 and 42.5 us, 320 38.1 and 34.4;
     // sequential draws T = 0.7, 384 parents 56.2 and 46.5, 450 63.8 and 52.5.
-    const int fit = eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg);
+    // Where scratch is short, rows at any address plan for two workgroups per CU
+    // (three fit): ts_expand_noalloc's array then takes 3072 parents at V = 151937
+    // with sequential draws, 2816 with the chunks that three take.
+    const bool ragged_even = even_chunks && pl.path == EvalPath::kLdsRagged;
+    const int fit = ragged_even ? 2 : eval_blocks_per_cu(d->dtype, pl.ks, pl.NB, eval_mode, store_z, pl.path, 64 * pl.wpg);
     const int concurrent = device_cus() * (store_z ? fit : std::min(fit, 4));
     const int rounds = std::max(1, (pl.n_pgroups * s_min + concurrent - 1) / concurrent);
     S = std::max(1, rounds * concurrent / pl.n_pgroups);
@@ -274,7 +278,7 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
     if (S > 8 && !even_chunks && S < s_max) S &= ~7;
     if (even_chunks) {
       // chunks of one rounded-up length: fewer of them
-      const int quantum = lds ? 256 : 64;
+      const int quantum = pl.path == EvalPath::kLds ? 256 : 64;
       int vc = std::max((d->V + S - 1) / S, (d->V + kMaxChunks - 1) / kMaxChunks);
       vc = std::min(std::max((vc + quantum - 1) / quantum * quantum, 256), 4096);
       S = (d->V + vc - 1) / vc;
