@@ -629,7 +629,8 @@ __global__ __launch_bounds__(256) void expand_eval_kernel(const ExpandParams p) 
 // two buffers used alternately, so no registers hold prefetched data.  The W2
 // tile is laid out in 16-byte pieces in the exact order the A fragments are
 // read (piece (bb*KS + kk)*64 + lane), so every fragment read is one
-// conflict-free ds_read_b128.  Requires chunks of a multiple of 256 tokens.
+// conflict-free ds_read_b128.  Requires chunks of a multiple of 64 tokens, of
+// 256 with sequential draws (their block masses are summed over quads of steps).
 //
 // RAG: vocabularies that are no multiple of 8 tokens, whose rows of U start
 // at any 2-byte address.  A lane loads its run from the 4-byte boundary at or
@@ -782,11 +783,14 @@ void expand_eval_lds_kernel(const ExpandParams p) {
 
   const int tbeg = p.cm.begin(chunk);
   const int tend = min(p.cm.begin(chunk + 1), V);
-  // The first loads take two round trips: the parents, then the tiles and the
-  // E rows together (E before the tiles made it three: 2048 parents, T = 0.7,
-  // V = 128256 130.3 us in place of 128.0; the W2 tile before the parents, which
-  // then wait for it, as loads return in order: 31 parents, V = 15936, r = 128
-  // 14.8 us in place of 14.6).
+  // The first loads take two round trips: the parents, then the first tiles and
+  // the E rows together (E before the tiles made it three: 2048 parents, T =
+  // 0.7, V = 128256 130.3 us in place of 128.0; the W2 tile before the parents,
+  // which then wait for it, as loads return in order: 31 parents, V = 15936, r =
+  // 128 14.8 us in place of 14.6).  The second U tile follows the E rows: queued
+  // ahead of them it was waited for with them, and a launch of a few steps was
+  // slower than with E first (sequential draws, T = 0.7, V = 12288, r = 64, 64
+  // parents: E first 21.28 us, both U tiles before E 21.54, so 21.17).
   // W2: this wave loads pieces (wv*KS + j)*64 + lane of the tile: row
   // (n >> 2)*16 + bb*4 + (n & 3) of the step, 16 bytes at k = kk*32 + g*8.
   // U: tokens t0 + g*16 + 8h + [0, 8) of this lane's parent in block nb.
@@ -847,10 +851,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
     }
   };
   issue_w(w0, tbeg);
-  if (active) {
-    issue_u(ub0, ux0, tbeg);
-    if (tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
-  }
+  if (active) issue_u(ub0, ux0, tbeg);
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) F::load_row(E + (size_t)ptok[nb] * r, g, bfrag[nb]);
   // the E fragments are in registers before the first step: the compiler does
@@ -860,6 +861,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(bfrag[nb][kk]));
+  if (active && tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
 
   // Per parent (shared by its four lane groups): the reference of the sums,
   // in logit units, the level that triggers a raise, and the FMA addends
