@@ -233,13 +233,9 @@ __device__ __forceinline__ void put_bonus(const BonusBest& bt, const VFused& f, 
   }
 }
 
-// One level of the workgroup's walk; true if the walk goes on to another.  A
-// function of its own: as the body of a loop over the levels, the compiler
-// carried addresses, bounds and masks over the levels and spilled 79 to 151
-// registers in the middle of the work (64 requests, T = 0.7: 178 us); the
-// call saves 48 at its entry instead (157 us).
+// One level of the workgroup's walk; true if the walk goes on to another.
 template <typename TT, int NQ>
-__device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int levelv) {
+__device__ __forceinline__ bool fused_level(FusedArgPtr apv, int levelv) {
   using Q = typename TQuad<TT>::type;
   static_assert(4 * NQ <= 64, "a thread's tokens fit the 64-bit child mask");
   __shared__ Q tl[NQ * kVerifyThreads];  // each thread's target quads, [q][thread]
@@ -591,9 +587,16 @@ __device__ __attribute__((noinline)) bool fused_level(FusedArgPtr apv, int level
 }
 
 template <typename TT, int NQ>
+__device__ __attribute__((noinline)) bool fused_next_level(FusedArgPtr ap, int level) {
+  return fused_level<TT, NQ>(ap, level);
+}
+
+template <typename TT, int NQ>
 __global__ __launch_bounds__(kVerifyThreads) __attribute__((amdgpu_waves_per_eu(4))) void verify_fused_kernel(
     const VFusedArgs) {
-  for (int level = 0; fused_level<TT, NQ>((FusedArgPtr)__builtin_amdgcn_kernarg_segment_ptr(), level); ++level) {
+  const FusedArgPtr ap = (FusedArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  if (!fused_level<TT, NQ>(ap, 0)) return;
+  for (int level = 1; fused_next_level<TT, NQ>(ap, level); ++level) {
   }
 }
 
