@@ -844,15 +844,19 @@ VerifyLayout verify_layout_for(const ts_drafter* d, int cap, float T, size_t hav
 }
 
 // Waits until every item of a one-launch round has its result words in pinned
-// memory.  Polling them spares the runtime's report of the launch's end
-// between rounds (64 requests, V = 100003: 157 us against 148).  *failed: a
-// wait between the launch's workgroups ran out; the stream is then idle.
-// After 20 ms, more than any round takes, the wait goes through the runtime,
-// which reports a failed launch.
-int32_t wait_round(const uint64_t* done, int words, uint32_t epoch, const volatile int32_t* herr, hipStream_t s,
-                   bool* failed) {
+// memory.  poll: a round may follow, and polling the words spares it the
+// runtime's report of the launch's end (64 requests, V = 100003: 157 us against
+// 148).  A last round goes through the runtime at once: the end of the stream
+// has to be waited for anyway, and asked for only after the words have arrived
+// its report comes on top of the launch (11 requests of one node, V = 6976: 43.8
+// us polled, 41.1 so).  *failed: a wait between the launch's workgroups ran out;
+// the stream is then idle.  Polling gives up after 20 ms (the work that the
+// caller had queued on the stream before counts among them), and the runtime
+// then reports a failed launch.
+int32_t wait_round(const uint64_t* done, int words, uint32_t epoch, const volatile int32_t* herr, bool poll,
+                   hipStream_t s, bool* failed) {
   const auto t0 = std::chrono::steady_clock::now();
-  bool slow = false;
+  bool slow = !poll;
   int i = 0;
   for (unsigned n = 1; i < words && *herr == 0 && !slow; ++n) {
     const uint64_t w = __atomic_load_n(done + i, __ATOMIC_ACQUIRE);
@@ -1364,6 +1368,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   size_t clear = nslots * 8 + 4;
   uint32_t epoch = 1;
   std::vector<int> next, nodes, node_at((size_t)R * cap, kNextHost);
+  bool idle = false;  // the stream has been waited for since the last launch
   while (!active.empty()) {
     const int ni = (int)active.size();
     const FusedPlan fp = thread_state().verify_mode == TS_VERIFY_STAGED ? FusedPlan{false, 0, 0}
@@ -1390,6 +1395,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     const int nn = (int)nodes.size();
     // the nodes' items and, after them, their children's records
     int mmax = 0;
+    bool open = false;  // a walk can reach a node with children that is not among them
     auto build_items = [&] {
       VerifyNext* hnext = reinterpret_cast<VerifyNext*>(hitem + nn);
       for (int i = 0, z = 0; i < nn; ++i) {
@@ -1408,6 +1414,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
           nx.child_node[j] = ch[j];
           nx.child_path[j] = tree->path[row + ch[j]];
           nx.child_item[j] = kids.count(q, ch[j]) == 0 ? kNextLeaf : node_at[row + ch[j]];
+          open = open || nx.child_item[j] == kNextHost;
         }
         it.zrow = it.m > 0 ? z++ : -1;
         mmax = std::max(mmax, it.m);
@@ -1482,7 +1489,8 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       launch_verify_fused(fvp, f, bf16, s);
       TS_HIP(hipGetLastError());
       bool failed = false;
-      if ((rc = wait_round(done, ni * kDoneWords, epoch, herr, s, &failed)) != TS_OK) return rc;
+      idle = !open;
+      if ((rc = wait_round(done, ni * kDoneWords, epoch, herr, open, s, &failed)) != TS_OK) return rc;
       epoch += TS_MAX_D + 1;  // a walk's levels, and the leaf it ends at
       if (failed) {
         ++thread_state().fused_levels;
@@ -1496,6 +1504,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       launch_verify_level(vp, bf16, mmax, s);
       TS_HIP(hipGetLastError());
       TS_HIP(hipStreamSynchronize(s));
+      idle = true;
     }
     next.clear();
     int levels = 0;
@@ -1534,7 +1543,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     if (!staged) thread_state().fused_levels += levels;
     active.swap(next);
   }
-  TS_HIP(hipStreamSynchronize(s));
+  if (!idle) TS_HIP(hipStreamSynchronize(s));
   drain.armed = false;
   return TS_OK;
 }
