@@ -801,6 +801,15 @@ size_t fused_slot_words(int R) {
 // some 150 MB.
 constexpr size_t kAheadBytes = 144u << 20;
 constexpr int kAheadRows = 4096;
+// The first round, after which walks often end, looks ahead only to all the
+// nodes with children below the roots together, and only where their bytes are
+// few or worth the chance that a walk gets past its root: kRoundBytes stand for
+// the round then saved.  ts_verify with the roots alone and with all nodes: 4
+// requests of 64 nodes, V = 128256 (some 90 MB, 5 us), walks that end at the root
+// 70.0 and 71.6 us, that go on 117.3 and 93.1; 1 request of 64 nodes, V = 151936,
+// r = 256 (20 MB) 79.0 and 77.9, 92.3 and 68.7; 64 requests of 64 nodes, V = 65536,
+// as many rows as kAheadBytes hold, 103.4 and 140.6, 153.2 and 188.0.
+constexpr size_t kRoundBytes = 112u << 20, kFewBytes = 24u << 20;
 int verify_rows(const ts_drafter* d, int cap) {
   const long long nodes = (long long)d->R * std::max(cap - 1, 1);
   const long long ahead = std::min<long long>(kAheadRows, (long long)(kAheadBytes / ((size_t)d->V * 6)));
@@ -1236,9 +1245,11 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   if (target_dtype != TS_F32 && target_dtype != TS_BF16) return fail(TS_EINVAL, "unknown target dtype %d", target_dtype);
   if (!(T >= 0.0f) || !std::isfinite(T)) return fail(TS_EINVAL, "T must be finite and >= 0");
   const int R = d->R, cap = tree->cap, V = d->V;
+  size_t tree_nodes = 0;
   for (int q = 0; q < R; ++q) {
     const int n = tree->n[q];
     if (n < 0 || n >= cap) return fail(TS_EINVAL, "tree n[%d]=%d outside [0, cap)", q, n);
+    tree_nodes += n;
     for (int i = 1; i <= n; ++i) {
       const size_t o = (size_t)q * cap + i;
       const int pa = tree->parent[o];
@@ -1354,8 +1365,6 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   VerifyResult* res = reinterpret_cast<VerifyResult*>(hs + hs_par + hs_nodes);
   uint64_t* done = reinterpret_cast<uint64_t*>(hs + hs_par + hs_nodes + hs_res);
   volatile int32_t* herr = reinterpret_cast<volatile int32_t*>(hs + hs_par + hs_nodes + hs_res + hs_done);
-  // children of every node in creation order (= draw order)
-  const KidIndex& kids = kid_index(tree);
   // the one-launch levels' slots and flag start the call at zero; each
   // level of a launch tags its slot words with an epoch of its own
   uint64_t* dslots = reinterpret_cast<uint64_t*>(ws + vl.off_sync);
@@ -1367,6 +1376,36 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   void* clear_at = dslots;
   size_t clear = nslots * 8 + 4;
   uint32_t epoch = 1;
+  // the rows in hpar and, with them, b bytes of the pinned buffer at h to the
+  // device, what has to be cleared, and the rows' logits
+  auto queue_rows = [&](int nz, const void* h, void* to, size_t b) -> int32_t {
+    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), clear_at, clear, s, h, to, b);
+    TS_HIP(hipGetLastError());
+    clear_at = derr;
+    clear = 4;
+    if (nz == 0) return TS_OK;
+    const Plan pl = make_plan(d, nz, T, TS_SAMPLER_GUMBEL, true);
+    launch_eval(d, eval_params(d, reinterpret_cast<const ts_parent*>(ws + vl.off_par), nz, T, seed, pl, nullptr, zbuf), pl,
+                s);
+    TS_HIP(hipGetLastError());
+    return TS_OK;
+  };
+  // Of trees so large that their rows (one for every fourth node, at the least
+  // to be expected) are more than a round is worth, the first recompute is queued
+  // before they are indexed, which takes the host some 10 us: its rows are the
+  // roots of the trees with children (n > 0), in request order.
+  const bool roots_first = tree_nodes / 4 * V * 6 > kRoundBytes;
+  if (roots_first) {
+    int nz = 0;
+    for (int q = 0; q < R; ++q) {
+      const size_t o = (size_t)q * cap;
+      if (tree->n[q] > 0) hpar[nz++] = ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]};
+    }
+    if ((rc = queue_rows(nz, nullptr, nullptr, 0)) != TS_OK) return rc;
+  }
+  // children of every node in creation order (= draw order)
+  const KidIndex& kids = kid_index(tree);
+  bool first = true;
   std::vector<int> next, nodes, node_at((size_t)R * cap, kNextHost);
   bool idle = false;  // the stream has been waited for since the last launch
   while (!active.empty()) {
@@ -1379,17 +1418,41 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     // children, breadth first; the rows of those with children in that order
     nodes.clear();
     int nz = 0;
+    const bool queued = first && roots_first;  // (the rows of its nodes)
     auto add_node = [&](int q, int node) {
       const size_t o = (size_t)q * cap + node;
       node_at[o] = (int)nodes.size();
       nodes.push_back((int)o);
-      if (kids.count(q, node) > 0) hpar[nz++] = ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]};
+      if (kids.count(q, node) == 0) return;
+      if (!queued) hpar[nz] = ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]};
+      ++nz;
     };
     for (int q : active) add_node(q, cur[q]);
-    for (size_t i = 0; ahead && i < nodes.size() && nz < vl.zrows; ++i) {
+    int most = ahead ? vl.zrows : 0;  // rows
+    if (queued) {
+      most = 0;
+    } else if (first && most > 0) {
+      // the nodes with children below the roots, and the chance that every walk
+      // ends at its root or at a leaf below it, from the draft's estimate of each
+      // child's survival (one half where the tree carries none)
+      size_t below = 0;
+      float stay = 1.0f;
+      for (int q = 0; q < R; ++q)
+        for (int i = 1; i <= tree->n[q]; ++i) {
+          if (kids.count(q, i) == 0) continue;
+          ++below;
+          const size_t o = (size_t)q * cap + i;
+          if (tree->parent[o] != 0) continue;
+          const float ls = tree->log_surv ? tree->log_surv[o] : NAN;
+          stay *= 1.0f - (ls <= 0.0f ? expf(ls) : 0.5f);
+        }
+      const double worth = std::max((1.0 - stay) * kRoundBytes, (double)kFewBytes);
+      if ((double)below * V * 6 > worth || nz + below > (size_t)most) most = 0;
+    }
+    for (size_t i = 0; i < nodes.size() && nz < most; ++i) {
       const int q = nodes[i] / cap, p = nodes[i] % cap;
       const int* ch = kids.first(q, p);
-      for (int j = 0, m = std::min(kids.count(q, p), TS_MAX_K); j < m && nz < vl.zrows; ++j)
+      for (int j = 0, m = std::min(kids.count(q, p), TS_MAX_K); j < m && nz < most; ++j)
         if (kids.count(q, ch[j]) > 0) add_node(q, ch[j]);
     }
     const int nn = (int)nodes.size();
@@ -1433,19 +1496,10 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     // large round are built and copied while it runs; a small one's, which take
     // the host a microsecond, go with the parents, a launch less (one request
     // of 5 nodes, V = 6000: 47.6 us apart, 44.5 together).
-    const bool together = nn <= 32;
+    const bool together = !queued && nn <= 32;
+    first = false;
     if (together) build_items();
-    launch_verify_stage_in(hpar, ws + vl.off_par, nz * sizeof(ts_parent), clear_at, clear, s, hitem, ditems,
-                           together ? items_bytes : 0);
-    TS_HIP(hipGetLastError());
-    clear_at = derr;
-    clear = 4;
-    if (nz > 0) {
-      const Plan pl = make_plan(d, nz, T, TS_SAMPLER_GUMBEL, true);
-      launch_eval(d, eval_params(d, reinterpret_cast<const ts_parent*>(ws + vl.off_par), nz, T, seed, pl, nullptr, zbuf),
-                  pl, s);
-      TS_HIP(hipGetLastError());
-    }
+    if (!queued && (rc = queue_rows(nz, hitem, ditems, together ? items_bytes : 0)) != TS_OK) return rc;
     if (!together) {
       build_items();
       launch_verify_stage_in(hitem, ditems, items_bytes, nullptr, 0, s);
