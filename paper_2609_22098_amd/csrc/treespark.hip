@@ -1492,11 +1492,12 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     const size_t items_bytes = nn * (sizeof(VerifyItem) + sizeof(VerifyNext));
     // Every workgroup of the recompute reads all of its rows' parents: they
     // are copied to the device first, with the clearing (594 workgroups x 64
-    // parents out of pinned memory took it from 22 to 31 us).  The items of a
-    // large round are built and copied while it runs; a small one's, which take
-    // the host a microsecond, go with the parents, a launch less (one request
-    // of 5 nodes, V = 6000: 47.6 us apart, 44.5 together).
-    const bool together = !queued && nn <= 32;
+    // parents out of pinned memory took it from 22 to 31 us).  The items go with
+    // them, a launch less between the recompute and the walk (one request of 5
+    // nodes, V = 6000: 47.6 us apart, 44.5 together; 64 requests whose trees have
+    // 148 nodes in all, V = 151936: 87.5 and 84.4), unless they are so many that the
+    // recompute would wait for the host.
+    const bool together = !queued && nn <= 256;
     first = false;
     if (together) build_items();
     if (!queued && (rc = queue_rows(nz, hitem, ditems, together ? items_bytes : 0)) != TS_OK) return rc;
