@@ -787,10 +787,8 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   // the E rows together (E before the tiles made it three: 2048 parents, T =
   // 0.7, V = 128256 130.3 us in place of 128.0; the W2 tile before the parents,
   // which then wait for it, as loads return in order: 31 parents, V = 15936, r =
-  // 128 14.8 us in place of 14.6).  The second U tile follows the E rows: queued
-  // ahead of them it was waited for with them, and a launch of a few steps was
-  // slower than with E first (sequential draws, T = 0.7, V = 12288, r = 64, 64
-  // parents: E first 21.28 us, both U tiles before E 21.54, so 21.17).
+  // 128 14.8 us in place of 14.6).  In short chunks the second U tile follows the E
+  // rows: queued ahead of them it is waited for with them (late_u below).
   // W2: this wave loads pieces (wv*KS + j)*64 + lane of the tile: row
   // (n >> 2)*16 + bb*4 + (n & 3) of the step, 16 bytes at k = kk*32 + g*8.
   // U: tokens t0 + g*16 + 8h + [0, 8) of this lane's parent in block nb.
@@ -850,8 +848,16 @@ void expand_eval_lds_kernel(const ExpandParams p) {
       if constexpr (RAG) lds_buf4_asm(usrc, uoff[nb], t0 * 2 + 32, ux + wv * kX + nb * 64);
     }
   };
+  // The second U tile after the E rows, in chunks of few steps, and ahead of them.
+  // ts_expand: sequential draws, T = 0.7, r = 64, 64 parents, V = 12288 (4 steps) 21.15
+  // and 21.49 us, V = 151936 (12) 28.8 and 29.4; Gumbel, T = 0.7, 2048 parents (76)
+  // 251.7 and 249.4; at r = 256, T = 1, 128 parents of a request (10) 47.4 and 46.4.
+  const bool late_u = tend - tbeg <= (KS == 8 ? 512 : 768);
   issue_w(w0, tbeg);
-  if (active) issue_u(ub0, ux0, tbeg);
+  if (active) {
+    issue_u(ub0, ux0, tbeg);
+    if (!late_u) issue_u(ub1, ux1, tbeg + 64);
+  }
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) F::load_row(E + (size_t)ptok[nb] * r, g, bfrag[nb]);
   // the E fragments are in registers before the first step: the compiler does
@@ -861,7 +867,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) asm volatile("" ::"v"(bfrag[nb][kk]));
-  if (active && tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
+  if (late_u && active && tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
 
   // Per parent (shared by its four lane groups): the reference of the sums,
   // in logit units, the level that triggers a raise, and the FMA addends
