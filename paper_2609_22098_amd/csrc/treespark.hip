@@ -412,12 +412,13 @@ ExpandParams eval_params(const ts_drafter* d, const ts_parent* parents, int P, f
 
 // Both passes of one expansion; all arguments already checked.
 // P_dev (optional): the device holds the parent count (<= P); P then sizes
-// the grids and the plan takes the most chunks.
+// the grids, and the plan takes the most chunks unless P is close to the count
+// (tight).
 int32_t run_expand(const ts_drafter* d, const ts_parent* parents, int P, ts_calib calib, int k,
                    float T, uint64_t seed, int sampler, const ts_expand_out* out, char* ws,
-                   hipStream_t s, const int* P_dev = nullptr, bool even_chunks = false) {
+                   hipStream_t s, const int* P_dev = nullptr, bool even_chunks = false, bool tight = false) {
   if (P == 0) return TS_OK;
-  const Plan pl = make_plan(d, P, T, sampler, false, false, P_dev != nullptr, even_chunks);
+  const Plan pl = make_plan(d, P, T, sampler, false, false, P_dev && !tight, even_chunks);
   ExpandParams ep = eval_params(d, parents, P, T, seed, pl, ws, nullptr);
   ep.P_dev = P_dev;
   hipEvent_t* ev = reinterpret_cast<hipEvent_t*>(out->events);
@@ -609,6 +610,12 @@ int32_t build_tree_device(const ts_drafter* d, const int32_t* anchor, const std:
   launch_wave_init(wp, s);
   TS_HIP(hipGetLastError());
 
+  // A chain (K = 1) has as many parents as the wave before until a price stops
+  // it: its waves take the plan of that count.  With the most chunks, 256 requests
+  // at V = 151936, r = 128 made 1024 workgroups where 768 fit the chip (16 waves of
+  // sequential draws, T = 1: 1064 us, so 918; 198 chunks of rounded-up length 1061),
+  // 600 at V = 64000, r = 64 1027 and 873.
+  const bool tight = K == 1;
   // queue wave w: expansion of par[w & 1] (at most Pub parents; the device
   // holds the count) and the control step, which also writes the next
   // wave's size into hcnt[w + 1] (pinned, -1 until then).  The host polls
@@ -617,7 +624,7 @@ int32_t build_tree_device(const ts_drafter* d, const int32_t* anchor, const std:
   for (int i = 0; i < D + 2; ++i) hcnt[i] = -1;
   auto queue_wave = [&](int w, int Pub) -> int32_t {
     int32_t r = run_expand(d, wp.par[w & 1], Pub, calib, K, T, seed, sampler, &eo, ws + bl.off_exp, s,
-                           reinterpret_cast<const int*>(wp.pcount + w));
+                           reinterpret_cast<const int*>(wp.pcount + w), false, tight);
     if (r != TS_OK) return r;
     launch_wave_control(wp, w, s);
     TS_HIP(hipGetLastError());
