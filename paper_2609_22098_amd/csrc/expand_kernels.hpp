@@ -851,9 +851,9 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   // The second U tile after the E rows, in chunks of few steps, and ahead of them.
   // ts_expand: sequential draws, T = 0.7, r = 64, 64 parents, V = 12288 (4 steps) 21.1
   // and 21.4 us, V = 151936 (12) 28.8 and 29.5; Gumbel, T = 0.7, 2048 parents (76)
-  // 251.7 and 249.4; at r = 256, where the E rows are the longer loads, T = 1, 128
-  // parents of a request (10) 47.4 and 46.4.
-  const bool late_u = KS < 8 && tend - tbeg <= 768;
+  // 251.7 and 249.4; at r = 256, T = 1, 128 parents of a request (10) with Gumbel
+  // draws 47.4 and 46.4, 64 sequential ones (12) 43.0 and 43.5.
+  const bool late_u = (KS < 8 || SEQ) && tend - tbeg <= 768;
   issue_w(w0, tbeg);
   if (active) {
     issue_u(ub0, ux0, tbeg);
