@@ -288,14 +288,16 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   // Where every workgroup has a CU to itself the longest chunk counts, and with
   // units of 256 tokens as many chunks as their limit allows often leave it no
   // shorter than fewer would: V = 151936 is 82 chunks of three units and 174 of
-  // two, or 198 of three.  The fewer cost less in the merge and the draws
-  // (ts_expand, T = 0.7, r = 64, the most and the fewest chunks: 1 parent 25.6 and
-  // 25.2 us, 16 parents 26.4 and 25.9, 4 parents at V = 160000 24.5 and 23.8; at
-  // V = 66000, 256 and 129 chunks, 23.2 and 23.4).  Units of 64 tokens keep the
-  // most: f32, 2 parents, V = 150000 50.0 and 50.9.
+  // two, or 198 of three.  The fewer cost less in the merge and the draws, unless
+  // they are so few that they leave much of the chip idle (ts_expand, the most and
+  // the fewest chunks: T = 0.7, r = 64, 1 parent 25.6 and 25.2 us, 16 parents 26.4 and
+  // 25.9, 4 parents at V = 160000 24.5 and 23.8, at V = 110000 (215 of 256), r = 128
+  // 27.2 and 26.9, 17 parents at V = 140000 (183), K = 16 38.8 and 38.2; T = 1, 2 parents
+  // at V = 75200 (147), r = 256, K = 16 52.6 and 55.0, at V = 66000 (129) 21.1 and 21.4).  Units of 64 tokens keep the most: f32, 2 parents,
+  // V = 150000 50.0 and 50.9.
   if (!sizing_only && !max_chunks && unit == 256 && (long long)pl.S * pl.n_pgroups <= device_cus()) {
-    const int longest = (units + pl.S - 1) / pl.S;
-    pl.S = (units + longest - 1) / longest;
+    const int longest = (units + pl.S - 1) / pl.S, fewest = (units + longest - 1) / longest;
+    if (fewest * 10 >= pl.S * 7) pl.S = fewest;
   }
   pl.S8 = ((pl.S + 7) / 8) * 8;
   pl.cm = ChunkMap{unit, units / pl.S, units % pl.S};

@@ -7,9 +7,9 @@ from test_gpu_expand import _expand_and_compare, torch  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# V: 257 units of 256 tokens (one more than the most chunks: 129 of two units), 511 and 513 (two and three units), an
-# odd vocabulary of three; one parent, a block and a workgroup of them, one more; f32 keeps the most chunks
-@pytest.mark.parametrize("V,dtype", [(65792, "bf16"), (130816, "bf16"), (131328, "bf16"), (140001, "bf16"), (66000, "f32")])
+# V: units of 256 tokens: 257 (one more than the most chunks, which stay), 385 (193 chunks of two), 511 (256), 577 (193 of
+# three), an odd vocabulary of 594; one parent, a block and a workgroup of them, one more; f32 keeps the most chunks
+@pytest.mark.parametrize("V,dtype", [(65792, "bf16"), (98560, "bf16"), (130816, "bf16"), (147712, "bf16"), (151937, "bf16"), (66000, "f32")])
 @pytest.mark.parametrize("P", [1, 16, 64, 65])
 @pytest.mark.parametrize("T", [0.7, 1.0])
 def test_few_parents(torch, V, dtype, P, T):  # noqa: F811
