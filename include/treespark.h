@@ -241,6 +241,12 @@ int32_t ts_build_tree(const ts_drafter* d, const int32_t* anchor, const float* t
                       int32_t sampler, ts_tree* out, const ts_tree* device_out, void* workspace,
                       size_t workspace_bytes, void* stream);
 
+/* Bytes of device workspace ts_verify takes for trees of cap rows.  At T > 0 it
+ * holds the recomputed logits of the nodes that one launch may walk to: one row
+ * of V floats per request, and up to about 100 MB more for nodes below the walks
+ * (64 requests, V = 151936: 39 MB and about 100 in all).  A smaller workspace of
+ * at least ts_verify_workspace_size(d, 1, T) bytes is accepted: the walks are the
+ * same, with more launches. */
 size_t ts_verify_workspace_size(const ts_drafter* d, int32_t cap, float T);
 
 /*
@@ -259,7 +265,8 @@ size_t ts_verify_workspace_size(const ts_drafter* d, int32_t cap, float T);
  *           p_{j+1} = norm(max(p_j - q_j, 0)); the bonus is a Gumbel-max draw
  *           from the final residual.
  * tree is the HOST tree from ts_build_tree (tree->R == d->R, tree->cap ==
- * cap of target).  path_nodes [R][TS_MAX_D], path_len [R], bonus [R] are
+ * cap of target); of its log_surv (may be NULL) only how many nodes' logits are
+ * recomputed ahead depends, not the walk.  path_nodes [R][TS_MAX_D], path_len [R], bonus [R] are
  * HOST outputs (node indices into the tree).  Synchronises `stream`.
  */
 int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target,

@@ -22,10 +22,11 @@
 // item's next node: its workgroups go on there without the host.  Items walk
 // independently, and a level taken this way costs the loads and pass A
 // (about 10 us) instead of a recompute, a launch and the host's turn around
-// (about 35 us): 64 requests with trees of up to 8 nodes (V = 151936, bf16, T
-// = 0.7) went from 169 to 131 us, one request with 64 nodes from 126 to 81.  Consecutive levels use the two halves of the item's slots in
-// turn: a workgroup can be one level ahead of another (which still reads the
-// level's words), never two.
+// (about 35 us).  With a launch per level and with this, 64 requests with trees of
+// up to 8 nodes (V = 151936, bf16, T = 0.7) take 187 and 110 us, one request with
+// 64 nodes (V = 128256) 148 and 78.  Consecutive levels use the two halves of the
+// item's slots in turn: a workgroup can be one level ahead of another (which still
+// reads the level's words), never two.
 //
 // The host sizes the grid to
 // what the device holds at once, so every workgroup is resident and every wait
@@ -586,6 +587,13 @@ __device__ __forceinline__ bool fused_level(FusedArgPtr apv, int levelv) {
   return false;
 }
 
+// The levels after the first are calls of a function: as the body of a loop over
+// the levels, the compiler carried addresses, bounds and masks over them and
+// spilled 79 to 151 registers in the middle of the work (64 requests, T = 0.7:
+// 178 us).  A call saves some 50 registers per lane at its entry, 50 MB of scratch
+// written and read back for 1024 workgroups, so the first level, at which many
+// walks end, is the kernel's own body (that measurement's case 125 us with every
+// level a call, 115 so; 64 requests whose trees have 148 nodes 96 and 89).
 template <typename TT, int NQ>
 __device__ __attribute__((noinline)) bool fused_next_level(FusedArgPtr ap, int level) {
   return fused_level<TT, NQ>(ap, level);

@@ -37,10 +37,11 @@ __device__ __forceinline__ float target_at(const TT* row, int y) {
 
 // Four tokens of a row that may start at any element: vector loads need only
 // 4-byte alignment.  bf16 at an odd 2-byte address: the words from the 4-byte
-// boundary before it and the quad's last token, shifted by 16 bits (nothing
-// outside the array is read).  Against four loads of one token each,
-// ts_verify at T = 0.7 for 64 requests, V = 100003 (bf16 target), went from 261
-// to 187 us, with the recompute on the LDS kernel.
+// boundary before it and the quad's last token, shifted by 16 bits.  (A bf16
+// array that itself starts at an odd address has the two bytes before it read
+// with its first token's word, and shifted out.)  Against four loads of one
+// token each, ts_verify at T = 0.7 for 64 requests, V = 100003 (bf16 target), went
+// from 261 to 187 us, with the recompute on the LDS kernel.
 typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4 quad_words(const float* p) { return *reinterpret_cast<const f32x4_a4*>(p); }
