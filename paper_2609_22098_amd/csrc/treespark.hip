@@ -1289,15 +1289,27 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     // nodes, V = 151936 bf16 and V = 100001 f32: with 96 MB for a round's levels
     // together 56.7 and 55.4 us, with 72 MB for each 44.3 and 49.7.
     constexpr size_t kGreedyBytes = 72u << 20, kGreedyRows = 1u << 20;
-    const KidIndex& kids = kid_index(tree);  // children of every node in creation order
     const bool bf16 = target_dtype == TS_BF16;
     const size_t row_bytes = (size_t)V * (bf16 ? 2 : 4);
-    std::vector<int> cur(R, 0), active(R), rows, known((size_t)R * cap, -1);
+    // All rows of trees that have no more than two levels' bytes are one round's,
+    // listed as they stand, and the trees are indexed while the launch runs: many
+    // short rows cost the host more than the chip (V = 1024, bf16, 64 trees of 64
+    // nodes gathered level by level 51.6 us, so 36.1; 256 of 200 331 and 169).
+    const size_t all = tree_nodes + R;
+    const bool every = all * row_bytes <= 2 * kGreedyBytes && all <= kGreedyRows;
+    const KidIndex* kids_at = every ? nullptr : &kid_index(tree);  // children of every node in creation order
+    std::vector<int> cur(R, 0), active(R), rows, known(every ? 0 : (size_t)R * cap, -1), start(every ? R : 0);
+    rows.reserve(every ? all : 0);
     for (int q = 0; q < R; ++q) active[q] = q;
     while (!active.empty()) {
       rows.clear();
-      for (int q : active) rows.push_back(q * cap + cur[q]);
-      for (size_t level = 0;;) {
+      for (int q = 0; every && q < R; ++q) {
+        start[q] = (int)rows.size();
+        for (int i = 0; i <= tree->n[q]; ++i) rows.push_back(q * cap + i);
+      }
+      for (size_t i = 0; !every && i < active.size(); ++i) rows.push_back(active[i] * cap + cur[active[i]]);
+      for (size_t level = 0; !every;) {
+        const KidIndex& kids = *kids_at;
         const size_t end = rows.size();
         size_t more = 0;
         for (size_t i = level; i < end; ++i) more += kids.count(rows[i] / cap, rows[i] % cap);
@@ -1320,12 +1332,14 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       launch_verify_argmax(target, bf16, V, reinterpret_cast<const int*>(hs), nrows, nc,
                            reinterpret_cast<ArgmaxPart*>(hs + hs_rows), s);
       TS_HIP(hipGetLastError());
-      for (int i = 0; i < nrows; ++i) known[rows[i]] = i;
+      for (int i = 0; !every && i < nrows; ++i) known[rows[i]] = i;
+      if (!kids_at) kids_at = &kid_index(tree);
+      const KidIndex& kids = *kids_at;
       TS_HIP(hipStreamSynchronize(s));
       size_t left = 0;
       for (int q : active) {
         bool done = false;
-        for (int i; !done && (i = known[(size_t)q * cap + cur[q]]) >= 0;) {
+        for (int i; !done && (i = every ? start[q] + cur[q] : known[(size_t)q * cap + cur[q]]) >= 0;) {
           const ArgmaxPart* pi = part + (size_t)i * nc;
           ArgmaxPart best = pi[0];
           for (int c = 1; c < nc; ++c)
@@ -1346,7 +1360,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
         if (!done) active[left++] = q;
       }
       active.resize(left);
-      for (int i = 0; i < nrows; ++i) known[rows[i]] = -1;  // the parts go with the next round's
+      for (int i = 0; !every && i < nrows; ++i) known[rows[i]] = -1;  // the parts go with the next round's
     }
     drain.armed = false;
     return TS_OK;
