@@ -745,6 +745,34 @@ const KidIndex& kid_index(const ts_tree* t) {
   return k;
 }
 
+// Where the nodes of a round are among its items (kNextHost: not there), by
+// request * cap + node.  The array is kept per thread: a verification sets and
+// clears the few that it uses.
+class NodeMarks {
+ public:
+  explicit NodeMarks(size_t n) : at_(array()) {
+    if (at_.size() < n) at_.resize(n, kNextHost);
+  }
+  ~NodeMarks() { clear(); }
+  int operator[](size_t o) const { return at_[o]; }
+  void set(size_t o, int v) {
+    set_.push_back(o);
+    at_[o] = v;
+  }
+  void clear() {
+    for (size_t o : set_) at_[o] = kNextHost;
+    set_.clear();
+  }
+
+ private:
+  static std::vector<int>& array() {
+    thread_local std::vector<int> at;
+    return at;
+  }
+  std::vector<int>& at_;
+  std::vector<size_t> set_;
+};
+
 struct VerifyLayout {
   size_t off_pa, off_zp, off_bp, off_cst, off_rec, off_sync;
   // the logit rows of a round's nodes, the parents they are recomputed from
@@ -819,6 +847,8 @@ constexpr int kAheadRows = 4096;
 // r = 256 (20 MB) 79.0 and 77.9, 92.3 and 68.7; 64 requests of 64 nodes, V = 65536,
 // as many rows as kAheadBytes hold, 103.4 and 140.6, 153.2 and 188.0.
 constexpr size_t kRoundBytes = 112u << 20, kFewBytes = 24u << 20;
+// Nodes that take the host some 35 us to index.
+constexpr size_t kManyNodes = 8192;
 int verify_rows(const ts_drafter* d, int cap) {
   const long long nodes = (long long)d->R * std::max(cap - 1, 1);
   const long long ahead = std::min<long long>(kAheadRows, (long long)(kAheadBytes / ((size_t)d->V * 6)));
@@ -1414,10 +1444,10 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     return TS_OK;
   };
   // Of trees so large that their rows (one for every fourth node, at the least
-  // to be expected) are more than a round is worth, the first recompute is queued
-  // before they are indexed, which takes the host some 10 us: its rows are the
-  // roots of the trees with children (n > 0), in request order.
-  const bool roots_first = tree_nodes / 4 * V * 6 > kRoundBytes;
+  // to be expected) are more than a round is worth, or that indexing them takes the
+  // host a round's time, the first recompute is queued before that: its rows are
+  // the roots of the trees with children (n > 0), in request order.
+  const bool roots_first = tree_nodes / 4 * V * 6 > kRoundBytes || tree_nodes > kManyNodes;
   if (roots_first) {
     int nz = 0;
     for (int q = 0; q < R; ++q) {
@@ -1429,7 +1459,9 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
   // children of every node in creation order (= draw order)
   const KidIndex& kids = kid_index(tree);
   bool first = true;
-  std::vector<int> next, nodes, node_at((size_t)R * cap, kNextHost);
+  std::vector<int> next;
+  std::vector<size_t> nodes;  // request * cap + node
+  NodeMarks node_at((size_t)R * cap);
   bool idle = false;  // the stream has been waited for since the last launch
   while (!active.empty()) {
     const int ni = (int)active.size();
@@ -1444,8 +1476,8 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     const bool queued = first && roots_first;  // (the rows of its nodes)
     auto add_node = [&](int q, int node) {
       const size_t o = (size_t)q * cap + node;
-      node_at[o] = (int)nodes.size();
-      nodes.push_back((int)o);
+      node_at.set(o, (int)nodes.size());
+      nodes.push_back(o);
       if (kids.count(q, node) == 0) return;
       if (!queued) hpar[nz] = ts_parent{tree->token[o], tree->depth[o], q, 0.0f, tree->path[o]};
       ++nz;
@@ -1473,7 +1505,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
       if ((double)below * V * 6 > worth || nz + below > (size_t)most) most = 0;
     }
     for (size_t i = 0; i < nodes.size() && nz < most; ++i) {
-      const int q = nodes[i] / cap, p = nodes[i] % cap;
+      const int q = (int)(nodes[i] / cap), p = (int)(nodes[i] % cap);
       const int* ch = kids.first(q, p);
       for (int j = 0, m = std::min(kids.count(q, p), TS_MAX_K); j < m && nz < most; ++j)
         if (kids.count(q, ch[j]) > 0) add_node(q, ch[j]);
@@ -1485,12 +1517,12 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
     auto build_items = [&] {
       VerifyNext* hnext = reinterpret_cast<VerifyNext*>(hitem + nn);
       for (int i = 0, z = 0; i < nn; ++i) {
-        const int q = nodes[i] / cap;
+        const int q = (int)(nodes[i] / cap);
         const size_t row = (size_t)q * cap, o = nodes[i];
         VerifyItem it{};
         VerifyNext nx{};
         it.request = q;
-        it.node = nodes[i] % cap;
+        it.node = (int)(nodes[i] % cap);
         it.depth = tree->depth[o];
         it.path = tree->path[o];
         const int* ch = kids.first(q, it.node);
@@ -1507,7 +1539,7 @@ int32_t ts_verify(const ts_drafter* d, const ts_tree* tree, const void* target, 
         hitem[i] = it;
         hnext[i] = nx;
       }
-      for (int o : nodes) node_at[o] = kNextHost;
+      node_at.clear();
     };
     VerifyItem* ditems = reinterpret_cast<VerifyItem*>(ws + vl.off_items);
     VerifyNext* dnext = reinterpret_cast<VerifyNext*>(ditems + nn);
