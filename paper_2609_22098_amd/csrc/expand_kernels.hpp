@@ -852,8 +852,9 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   // ts_expand: sequential draws, T = 0.7, r = 64, 64 parents, V = 12288 (4 steps) 21.1
   // and 21.4 us, V = 151936 (12) 28.8 and 29.5; Gumbel, T = 0.7, 2048 parents (76)
   // 251.7 and 249.4; at r = 256, T = 1, 128 parents of a request (10) with Gumbel
-  // draws 47.4 and 46.4, 64 sequential ones (12) 43.0 and 43.5.
-  const bool late_u = (KS < 8 || SEQ) && tend - tbeg <= 768;
+  // draws 47.4 and 46.4, 64 sequential ones (12) 43.0 and 43.5.  Rows at any address
+  // with two blocks per wave do without the branch: 512 parents, V = 100003 67.1 and 66.6.
+  const bool late_u = (KS < 8 || SEQ) && !(RAG && NB == 2) && tend - tbeg <= 768;
   issue_w(w0, tbeg);
   if (active) {
     issue_u(ub0, ux0, tbeg);
