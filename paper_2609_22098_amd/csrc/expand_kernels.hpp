@@ -858,7 +858,7 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   issue_w(w0, tbeg);
   if (active) {
     issue_u(ub0, ux0, tbeg);
-    if (!late_u) issue_u(ub1, ux1, tbeg + 64);
+    if (!late_u && tbeg + 64 < tend) issue_u(ub1, ux1, tbeg + 64);
   }
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) F::load_row(E + (size_t)ptok[nb] * r, g, bfrag[nb]);
