@@ -853,7 +853,8 @@ void expand_eval_lds_kernel(const ExpandParams p) {
   // and 21.4 us, V = 151936 (12) 28.8 and 29.5; Gumbel, T = 0.7, 2048 parents (76)
   // 251.7 and 249.4; at r = 256, T = 1, 128 parents of a request (10) with Gumbel
   // draws 47.4 and 46.4, 64 sequential ones (12) 43.0 and 43.5.  Rows at any address
-  // with two blocks per wave do without the branch: 512 parents, V = 100003 67.1 and 66.6.
+  // with two blocks per wave, one set of buffers: 512 parents, V = 100003 53.2 and 53.0,
+  // 1024 parents 69.0 and 68.7, 600 parents, V = 151937 67.4 and 67.3.
   const bool late_u = (KS < 8 || SEQ) && !(RAG && NB == 2) && tend - tbeg <= 768;
   issue_w(w0, tbeg);
   if (active) {

@@ -293,8 +293,8 @@ Plan make_plan(const ts_drafter* d, int P, float T, int sampler, bool store_z = 
   // the fewest chunks: T = 0.7, r = 64, 1 parent 25.6 and 25.2 us, 16 parents 26.4 and
   // 25.9, 4 parents at V = 160000 24.5 and 23.8, at V = 110000 (215 of 256), r = 128
   // 27.2 and 26.9, 17 parents at V = 140000 (183), K = 16 38.8 and 38.2; T = 1, 2 parents
-  // at V = 75200 (147), r = 256, K = 16 52.6 and 55.0, at V = 66000 (129) 21.1 and 21.4).  Units of 64 tokens keep the most: f32, 2 parents,
-  // V = 150000 50.0 and 50.9.
+  // at V = 75200 (147), r = 256, K = 16 52.6 and 55.0, at V = 66000 (129) 21.1 and
+  // 21.4).  Units of 64 tokens keep the most: f32, 2 parents, V = 150000 50.0 and 50.9.
   if (!sizing_only && !max_chunks && unit == 256 && (long long)pl.S * pl.n_pgroups <= device_cus()) {
     const int longest = (units + pl.S - 1) / pl.S, fewest = (units + longest - 1) / longest;
     if (fewest * 10 >= pl.S * 7) pl.S = fewest;
